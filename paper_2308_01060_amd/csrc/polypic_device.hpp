@@ -81,11 +81,15 @@ __host__ __device__ constexpr bool has_mode(int kx, int ky, int kz) {
 // outside [0, n - 3] (or the position is not finite).
 __device__ __forceinline__ bool stencil_axis(float x, float o, float inv_dx, int n, int& b,
                                              float& t) {
-  const float u = __fmul_rn(__fsub_rn(x, o), inv_dx);
-  const float f = floorf(__fsub_rn(u, 0.5f));
+  // (the product must not be contracted into either subtraction, which the rounding
+  // intrinsics alone do not keep the compiler from: b and t would differ between kernels)
+#pragma clang fp contract(off)
+  const float d = x - o;
+  const float u = d * inv_dx;
+  const float f = floorf(u - 0.5f);
   const bool ok = (f >= 0.0f) && (f <= (float)(n - 3));
   b = ok ? (int)f : 0;
-  t = ok ? __fsub_rn(u, f + 1.0f) : 0.0f;
+  t = ok ? u - (f + 1.0f) : 0.0f;
   return ok;
 }
 
@@ -750,6 +754,36 @@ __device__ __forceinline__ void row_store_nt(float v, float* row, int n, int lan
 }
 __device__ __forceinline__ float row_load(const float* row, int n, int lane_byte_off) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row_rsrc(row, n), lane_byte_off, 0, 0));
+}
+
+// Staged rows out in whole lines, wherever the rows start: a wavefront writes n slots (n up
+// to 4 * kWave) of a row, in LDS in slot order, to row[0, n).  Body: whole 128-byte lines
+// (rows_body(n) slots, the same for every row) from the row's first line boundary on, four
+// slots per lane, streamed past the caches.  Ends: the up to 63 slots before and after the
+// body, one per lane.  Rows of P floats start on 64-byte boundaries only when 16 divides P;
+// written slot by lane, a wavefront's 256 bytes otherwise split 64-byte sectors with its
+// neighbours', and each part goes to memory by itself (measured, 84 rows of 4.0 M floats:
+// 251 us slot by lane when 32 divides P, 310 at 16, 495 at 8 and 580 at an odd P; in whole
+// lines 229 to 260 at any).
+constexpr int kLine = 32;  // floats
+typedef float Float4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ int rows_body(int n) { return max(n - (kLine - 1), 0) & ~(kLine - 1); }
+// slots before the row's first line boundary
+__device__ __forceinline__ int row_head(const float* row) {
+  return (int)(-(uint32_t)((uintptr_t)row >> 2) & (kLine - 1));
+}
+// lanes with 4 * lane < rows_body(n) call it
+__device__ __forceinline__ void row_store_body(const float* staged, float* row, int lane) {
+  const int at = row_head(row) + 4 * lane;
+  const float* const s = staged + at;
+  __builtin_nontemporal_store(Float4{s[0], s[1], s[2], s[3]},
+                              reinterpret_cast<Float4*>(row + at));
+}
+__device__ __forceinline__ void row_store_ends(const float* staged, float* row, int n, int body,
+                                               int lane) {
+  const int at = min(lane + (lane < row_head(row) ? 0 : body), n);  // (n: dropped)
+  row_store_nt(staged[min(at, n - 1)], row, n, at * (int)sizeof(float));
 }
 
 // popcount of the bits of `mask` below this lane
