@@ -113,7 +113,8 @@ P2GConfig to_config(const P2GChoice& c) {
 }
 
 std::atomic<int> g_g2p_sched{POLYPIC_SCHED_LINEAR};
-// lane-group size of the fused G2P2G kernel per mode count (0: the default, pairs)
+// lane-group size of the fused G2P2G kernel per mode count (0: the default, by each
+// chunk's cells, reported as pairs)
 std::atomic<int> g_fused_lane[28];
 std::atomic<int> g_fused_sched[28];  // POLYPIC_SCHED_LINEAR (the default) or _XCD
 
@@ -986,7 +987,7 @@ int32_t polypic_g2p2g(const polypic_grid* grid, int64_t P, int32_t n_modes, floa
   a.gp2 = grid_mom + 2 * N;
   a.status = status_dev;
   a.gstride = N;
-  a.lane_group = fused_lane_group(n_modes);
+  a.lane_group = g_fused_lane[n_modes].load();
   a.accumulate = accumulate != 0;
   a.sched = fused_sched(n_modes);
   a.regions = region_state;
@@ -1422,7 +1423,7 @@ int32_t polypic_batch_g2p2g(const polypic_batch* batch, int32_t n_modes, float d
   // cache between the passes, so neighbouring chunks share one L2 (measured, 64
   // scenes, 25.7 M particles: 3.81 -> 3.57 ms per graph step)
   a.sched = kSchedXcd;
-  a.lane_group = 2;
+  a.lane_group = 0;
   discard_stale_error();
   return from_hip(launch_g2p2g_batch(a, batch_table(batch), batch->n_scenes, n_modes,
                                      (hipStream_t)stream));

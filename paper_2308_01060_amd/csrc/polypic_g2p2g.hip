@@ -9,7 +9,7 @@
 //     coefficients, the advected position x' (and F', mass) at slot i;
 //   * P2G at x' with the coefficients still in registers: the stencil of x',
 //     the weighted mode rows, and the nodal mass and momentum streamed node by
-//     node into FP64 LDS bricks of 4^3-node tiles (lane pairs that share a
+//     node into FP64 LDS bricks around 4^3-node tiles (lane groups that share a
 //     base node add across lanes first), then one float atomic per brick node
 //     and channel into the next grid.
 //
@@ -18,63 +18,98 @@
 // drops from 40 + 24 n_modes to 28 + 12 n_modes bytes per particle.  The result
 // is the G2P call followed by the P2G call on its outputs, up to the order of
 // the floating-point sums.
+#include <type_traits>
+
 #include "polypic_internal.hpp"
 
 namespace polypic {
 
 namespace {
 
-// Slot of a thread: lane groups of G = 2^LG consecutive slots (which in cell
-// order usually share a cell, hence a base node), the groups of a wavefront
-// spread over the workgroup's chunk so that they sit in different cells and
-// their brick atomics do not collide.
-template <int LG, int NW>
-__device__ __forceinline__ int fused_slot(int tid) {
+// Slot of a thread: lane groups of 2^lg consecutive slots (which in cell order
+// usually share a cell, hence a base node), the groups of a wavefront spread over
+// the workgroup's chunk so that they sit in different cells and their brick
+// atomics do not collide.  The wavefronts' places rotate from one 64 slots to the
+// next: the slots of a wavefront then differ modulo 64, and its writes to a staging
+// row (one float per slot, in slot order) fall in 64 distinct LDS banks.
+template <int NW>
+__device__ __forceinline__ int fused_slot(int tid, int lg) {
+  static_assert(NW == 4, "four wavefronts' groups of 2 or 4 lanes: 64 slots per 16 >> lg groups");
   const int lane = tid & (kWave - 1);
   const int wv = tid / kWave;
-  return (((lane >> LG) * NW + wv) << LG) | (lane & ((1 << LG) - 1));
+  const int group = lane >> lg;
+  return ((group * NW + ((wv + (group >> (4 - lg))) & (NW - 1))) << lg) | (lane & ((1 << lg) - 1));
 }
 
-// Position of slot s in a staging row (a permutation of each 32 slots).  The 64
-// slots one wavefront writes agree in their wavefront-index bits (LG, LG + 1) and
-// differ in bits 5-7, which a plain index drops from the bank number.  XORing bit 6,
-// and bits 5 ^ 7, into the wavefront-index bits puts the writes of each half
-// wavefront on 32 distinct banks and those of the whole wavefront on 64, while a
-// read of 64 consecutive slots only permutes each half.  (Written for 256-thread
-// workgroups; any size stays a bijection.)
-template <int LG>
-__device__ __forceinline__ int stage_pos(int s) {
-  return s ^ (((s >> 6) & 1) << LG) ^ ((((s >> 7) ^ (s >> 5)) & 1) << (LG + 1));
-}
+// Bricks of the scatter.  A workgroup's slots are in the order of the positions before
+// the advection, so the 4^3-node tiles of those positions are runs of consecutive slots,
+// and one step moves a particle by less than a cell: a brick covers its tile's cells and
+// one cell around them (8^3 nodes).  A particle that crossed into a neighbouring tile
+// then stays in its own tile's brick.  With bricks of the tile alone (6^3 nodes), given to
+// the tiles of the new positions, such particles take a chunk past its bricks and go to
+// HBM, 27 atomics per channel each, and the call slows with the speed of the flow
+// (measured, 4.19 M particles, 4 modes, 0.1, 1.3 and 2.6 % of a cell per step and axis: 232,
+// 478 and 756 us; with these bricks 213, 249 and about 280).  The z stride spreads a half wavefront's
+// cells over the banks, as in the tile-only bricks.
+constexpr int kFuseN = kBrickN + 2;  // nodes per brick edge
+constexpr int kFuseSY = 8;
+constexpr int kFuseSZ = 68;
+constexpr int kFuseV = (kFuseN - 1) * (1 + kFuseSY + kFuseSZ) + 1;  // doubles per channel
+constexpr int kFuseNodes = kFuseN * kFuseN * kFuseN;
+// Channels a round of the scatter fills: two rounds of two channels let three bricks fit
+// where all four channels at once would leave two, and a chunk of a block's edge or of a
+// small scene touches three or four tiles (of a 16^3-cell block's slots, 4.5 % lie in the
+// third tile of their chunk or later, 0.9 % in the fourth or later).
+constexpr int kFuseCh = 2;
+constexpr int kFuseK = 3;  // bricks per workgroup
+constexpr int kFuseBrickF = (2 * kFuseK * kFuseCh * kFuseV + 63) / 64 * 64;  // in floats
+// Coefficients of the last component that the second half reads back from the LDS rows
+// they were staged in, instead of holding them in registers across the scatter of the
+// other channels: at 27 modes the 128 registers of 4 waves per SIMD otherwise spill, and
+// the spills' scratch traffic costs more than these reads (measured, 27 modes: 414 us at
+// 11 spilled registers, 385 at none; 776 and 718 for a batch of 6 M particles).
+template <int NR>
+constexpr int kFuseKept = NR > 8 ? 12 : 0;
+constexpr int kRuns = kWave;  // runs of equal tiles looked at per workgroup
+constexpr uint32_t kNoCell = 0xFFFFFFFFu;
+// first node of the 4^3 tile of a packed base node (10 bits an axis)
+__device__ __forceinline__ uint32_t tile_bits(uint32_t cell) { return cell & 0x3FCFF3FCu; }
+constexpr int kQuadCell = 10;  // particles per cell of a chunk from which quads fold
 
-// LDS (about 40 KB per 256-thread workgroup) allows 4 waves per SIMD; the launch
-// bound holds the registers to the 128 that allow them too.  At 27 modes that
-// spills 6 registers and still wins (measured, 4.19 M particles: 0.40 ms at 3
-// waves per SIMD without spills, 0.38 ms at 4).
-// LG: log2 of the lane-group size.  Pairs (LG = 1) are the default: where the vector
-// ALU is the tighter limit, one DPP fold per node value beats the two of quads
-// (measured, 27 modes, 4.19 M particles at 8 per cell: 0.369 -> 0.359 ms).  Quads
-// (LG = 2) spread a wavefront's groups 16 slots apart instead of 8, so that at 16
-// particles per cell two groups of a wavefront do not share a cell and its LDS
-// addresses; the fused autotuner picks between them on the caller's data.
-template <int NR, int BS, class Scenes, int LG>
+// LDS (about 40 KB per 256-thread workgroup at 27 modes) allows 4 waves per SIMD; the
+// launch bound holds the registers to the 128 that allow them too (measured, 4.19 M
+// particles: 0.40 ms at 3 waves per SIMD, 0.38 ms at 4).  With at most 8 modes 28 KB and
+// fewer registers allow 5.
+// Lane groups: a group whose particles share brick and base node adds its node values
+// across lanes first, and one lane does the atomics.  Pairs do best while the 32 pairs of
+// a wavefront fall in different cells (one DPP fold per node value instead of two); in
+// chunks whose cells hold more particles two pairs of a wavefront share a cell and its LDS
+// addresses, and quads do better.  Left to itself (lane_group 0) the kernel counts the
+// cells of each chunk and takes quads from kQuadCell particles per cell on (measured, pairs
+// and quads, 27 modes: 194 and 207 us at 8 per cell, 330 and 323 at 12, 457 and 419 at 16;
+// 4 modes: 238 and 203 at 12, 330 and 251 at 16).
+template <int NR, int BS, class Scenes, bool kLines>
 __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   constexpr int NW = BS / kWave;
-  static_assert(LG == 1 || LG == 2, "lane pairs or quads");
+  constexpr int K = kFuseK;
+  constexpr int kKept = kFuseKept<NR>;
   static_assert(!Scenes::kMany, "a workgroup's slots lie in one scene (OneScene, SceneChunks)");
-  __shared__ double brick[kBrickKMAX * 4 * kBrickV];  // [brick][channel][node]
-  __shared__ uint64_t tile_of[BS];                    // by processing slot
-  __shared__ int seg_of[BS];
-  __shared__ uint64_t seg_tile[kBrickKMAX];
-  __shared__ int wave_heads[NW];
-  __shared__ uint64_t run_tile[kWave];  // tile of each of the first 64 runs
-  __shared__ int run_brick[kWave];      // brick (distinct-tile index) of each run
-  __shared__ int n_bricks;
+  constexpr int kRows = NR + 1 > 10 ? NR + 1 : 10;  // staged: a component, or F and the mass
+  constexpr int kStage0 =  // floats
+      kFuseBrickF + kKept * BS > kRows * BS ? kFuseBrickF + kKept * BS - kRows * BS : 0;
+  __shared__ alignas(16) double lds_all[(kStage0 + kRows * BS) / 2];
+  static_assert(kStage0 % 4 == 0 && sizeof(lds_all) >= kFuseBrickF * sizeof(float), "layout");
+  double* const brick = lds_all;  // [brick][channel of the round][node]
+  __shared__ uint32_t cell_of[BS];  // by slot: base node before the advection, 10 bits an axis
+  __shared__ int16_t run_of[BS];    // by slot: its run of equal tiles
+  __shared__ int wave_heads[NW];    // heads of runs, and of cells << 16
+  __shared__ uint32_t run_tile[kRuns];  // tiles of the first runs, then of the bricks
+  __shared__ int run_brick[kRuns];      // brick (distinct-tile index) of each run
+  __shared__ int n_distinct;
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wv = tid / kWave;
-  const int slot = fused_slot<LG, NW>(tid);
   const size_t Ps = (size_t)a.P;
   // this workgroup's chunk (in launch order, or XCD-contiguous), its slots
   // [i0, i0 + n_slots) and the scene of the first
@@ -82,15 +117,17 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   if (ck.n <= 0) return;  // (whole workgroup: past the last chunk of a scene-chunked launch)
   const int64_t i0 = ck.i0;
   const int n_slots = ck.n;
-  const int64_t i = i0 + slot;
-  const bool in = slot < n_slots;
   const SceneGrid g = sc.grid(ck.s);  // uniform over the workgroup
   const int nx = g.nx, ny = g.ny, nz = g.nz;
   const int nxny = nx * ny;
-  // a caller permutation is clamped into [0, P): a bad one gives wrong results, never a fault
-  const int p = in ? (a.perm ? min(max(a.perm[i], 0), (int)(a.P - 1)) : (int)i) : 0;
 
   // ---------------------------------------------------------------- G2P
+  // Lane pairs to begin with; the chunk's cells may turn out to call for quads.
+  int lg = a.lane_group == 4 ? 2 : 1;
+  int slot = fused_slot<NW>(tid, lg);
+  bool in = slot < n_slots;
+  // a caller permutation is clamped into [0, P): a bad one gives wrong results, never a fault
+  int p = in ? (a.perm ? min(max(a.perm[i0 + slot], 0), (int)(a.P - 1)) : (int)(i0 + slot)) : 0;
   float xp[3] = {0.f, 0.f, 0.f};
   if (in) {
     xp[0] = a.x_in[p];
@@ -103,42 +140,128 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   ok &= stencil_axis(xp[1], g.oy, g.inv_dx, ny, b1, t1);
   ok &= stencil_axis(xp[2], g.oz, g.inv_dx, nz, b2, t2);
   if (in && !ok) raise_flag(a.status, kFlagRange);
-  const bool gather = in && ok;
+  bool gather = in && ok;
+  cell_of[slot] = gather ? (uint32_t)b0 | ((uint32_t)b1 << 10) | ((uint32_t)b2 << 20) : kNoCell;
+  float* const stage = reinterpret_cast<float*>(lds_all) + kStage0;
+  if (a.lane_group == 0) {  // (in case the slots are dealt out again)
+    stage[slot] = xp[0];
+    stage[BS + slot] = xp[1];
+    stage[2 * BS + slot] = xp[2];
+    stage[3 * BS + slot] = __int_as_float(p);
+  }
+  // every lane's stencil lies in the grid (a flagged or idle lane has base node
+  // 0 and the grid at least 3 nodes per axis), so the gathers need no branch;
+  // such lanes are zeroed afterwards, only in the wavefronts that hold one
+  int64_t vbase = g.node_off + (int64_t)(b2 * ny + b1) * nx + b0;
+  auto gather_nodes = [&](int ax, float(&v)[27]) {
+    const float* vg = a.gv + (size_t)ax * a.gstride + vbase;
+#pragma unroll
+    for (int jz = 0; jz < 3; ++jz)
+#pragma unroll
+      for (int jy = 0; jy < 3; ++jy)
+#pragma unroll
+        for (int jx = 0; jx < 3; ++jx) v[jx + 3 * jy + 9 * jz] = vg[jz * nxny + jy * nx + jx];
+  };
+  float v[27];
+  gather_nodes(0, v);
+
+  // While the first gathers are in flight: the chunk's runs of equal tiles in slot order
+  // (thread t looks at slot t), and its cells.
+  int n_runs = 0, cells = 0;
+  __syncthreads();
+  {
+    const uint32_t cell = cell_of[tid], before = tid > 0 ? cell_of[tid - 1] : kNoCell;
+    const bool some = cell != kNoCell;
+    const bool head = some && (before == kNoCell || tile_bits(before) != tile_bits(cell));
+    const unsigned long long hb = __ballot(head), cb = __ballot(some && before != cell);
+    if (lane == 0) wave_heads[wv] = __popcll(hb) | (__popcll(cb) << 16);
+    __syncthreads();
+    int pre = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int h = wave_heads[w];
+      pre += w < wv ? h & 0xFFFF : 0;
+      n_runs += h & 0xFFFF;
+      cells += h >> 16;
+    }
+    n_runs = __builtin_amdgcn_readfirstlane(n_runs);
+    cells = __builtin_amdgcn_readfirstlane(cells);
+    const int run = pre + lanes_below(hb) + (head ? 1 : 0) - 1;
+    run_of[tid] = (int16_t)run;  // (-1 before the first valid slot)
+    if (head && run < kRuns) run_tile[run] = tile_bits(cell);
+  }
+  if (a.lane_group == 0 && n_slots >= kQuadCell * cells) {  // (uniform)
+    lg = 2;
+    slot = fused_slot<NW>(tid, lg);
+    in = slot < n_slots;
+    xp[0] = stage[slot];
+    xp[1] = stage[BS + slot];
+    xp[2] = stage[2 * BS + slot];
+    p = __float_as_int(stage[3 * BS + slot]);
+    gather = cell_of[slot] != kNoCell;
+    stencil_axis(xp[0], g.ox, g.inv_dx, nx, b0, t0);
+    stencil_axis(xp[1], g.oy, g.inv_dx, ny, b1, t1);
+    stencil_axis(xp[2], g.oz, g.inv_dx, nz, b2, t2);
+    vbase = g.node_off + (int64_t)(b2 * ny + b1) * nx + b0;
+    gather_nodes(0, v);
+    __syncthreads();  // the stage is read
+  }
+  const bool quads = lg == 2;  // (uniform)
+  // Up to K runs of equal tiles take a brick each (in sorted order every tile is one
+  // run).  With more (also when the chunk is in no tile order, and a tile makes several
+  // runs) the first kRuns runs' tiles are deduplicated in order of appearance by
+  // wavefront 0, and the first K distinct ones take the bricks.
+  if (n_runs > K) {  // (uniform)
+    __syncthreads();
+    if (wv == 0) {
+      const int nr = n_runs < kRuns ? n_runs : kRuns;
+      const uint32_t mine = lane < nr ? run_tile[lane] : kNoCell;
+      int first_same = lane;  // first run with this run's tile
+      for (int q = nr - 1; q >= 0; --q)
+        if (q < lane && run_tile[q] == mine) first_same = q;
+      const bool first = lane < nr && first_same == lane;
+      const unsigned long long fb = __ballot(first);
+      // distinct index of a first run = first runs before it; a later run takes its
+      // first run's index (all lanes hold a value, so the shuffle is well defined)
+      const int d_first = lanes_below(fb);
+      const int d = __shfl(d_first, first_same, kWave);
+      if (lane < nr) run_brick[lane] = d;
+      if (first && d < K) run_tile[d] = mine;  // (d <= lane; every lane has read its own)
+      if (lane == 0) n_distinct = __popcll(fb);
+    }
+  }
 
   float c[3][27];  // the new coefficients, kept for the P2G half
   float xn[3];     // the advected position
   // Output rows go through LDS (the bricks are not in use yet) so that every
   // wavefront writes 64 consecutive slots (measured, 27 modes, 4.19 M particles:
-  // 2.0 ms with the rows written from the spread slots, 0.47 ms staged): row k of
-  // a round is stage[k * BS + stage_pos(slot)], read back at stage_pos(tid).
-  float* const stage = reinterpret_cast<float*>(brick);
-  static_assert(28 * BS * sizeof(float) <= sizeof(brick), "staging fits in the bricks");
-  const int64_t i_out = i0 + tid;  // slot this thread writes out
-  const int put = stage_pos<LG>(slot), get = stage_pos<LG>(tid);
-  // floats of this workgroup's rows that exist, and this thread's byte in a row
-  const int row_n = n_slots;
-  const int out_off = tid * (int)sizeof(float);
-  const bool out_ok = tid < n_slots;
+  // 2.0 ms with the rows written from the spread slots, 0.47 ms staged).  The last kKept
+  // rows lie past the bricks.
+  auto row_at = [&](int k) { return stage + k * BS; };
+  // `rows` staged rows out, row k from row_at(k0 + k) to dst(k): every thread its slot, or
+  // (kLines) in whole lines, a quarter of the rows per wavefront
+  const int wave = __builtin_amdgcn_readfirstlane(wv);
+  auto write_rows = [&](auto rows, int k0, auto dst) {
+    if constexpr (!kLines) {
+#pragma unroll
+      for (int k = 0; k < rows; ++k)
+        row_store_nt(row_at(k0 + k)[tid], dst(k), n_slots, tid * (int)sizeof(float));
+    } else {
+      const int body = rows_body(n_slots);  // (uniform)
+      auto each = [&](auto&& put) {
+#pragma unroll
+        for (int k = 0; k < rows; k += NW)
+          if (k + NW <= rows || k + wave < rows) put(row_at(k0 + k + wave), dst(k + wave));
+      };
+      if (4 * lane < body) each([&](const float* s, float* row) { row_store_body(s, row, lane); });
+      each([&](const float* s, float* row) { row_store_ends(s, row, n_slots, body, lane); });
+    }
+  };
   {
     const Proj1D px = proj_g2p(t0);
     const Proj1D py = proj_g2p(t1);
     const Proj1D pz = proj_g2p(t2);
-    const int64_t gbase = g.node_off + (int64_t)(b2 * ny + b1) * nx + b0;
-    // every lane's stencil lies in the grid (a flagged or idle lane has base node
-    // 0 and the grid at least 3 nodes per axis), so the gathers need no branch;
-    // such lanes are zeroed afterwards, only in the wavefronts that hold one
     const bool any_idle = __ballot(!gather) != 0ull;
-    auto gather_nodes = [&](int ax, float(&v)[27]) {
-      const float* vg = a.gv + (size_t)ax * a.gstride + gbase;
-#pragma unroll
-      for (int jz = 0; jz < 3; ++jz)
-#pragma unroll
-        for (int jy = 0; jy < 3; ++jy)
-#pragma unroll
-          for (int jx = 0; jx < 3; ++jx) v[jx + 3 * jy + 9 * jz] = vg[jz * nxny + jy * nx + jx];
-    };
-    float v[27];
-    gather_nodes(0, v);
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
       project_modes<NR>(v, px, py, pz, c[ax]);
@@ -154,20 +277,17 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       float x1 = fmaf(a.dt, c[ax][0], xp[ax]);
       x1 = fmaxf(x1, g.lo[ax]);
       xn[ax] = fminf(x1, g.hi[ax]);
-      // rows of this component: the NR coefficients and x'; written once, never
-      // re-read here, so streamed past the caches the gathers use
-      float* const co = a.coeff_out + (size_t)ax * NR * Ps + i0;  // this workgroup's slots
-      float* const xo = a.x_out + (size_t)ax * Ps + i0;
+      // rows of this component: x', then the NR coefficients; written once, never re-read
+      // here, so streamed past the caches the gathers use
+      row_at(0)[slot] = xn[ax];
 #pragma unroll
-      for (int r = 0; r < NR; ++r) stage[r * BS + put] = c[ax][r];
-      stage[NR * BS + put] = xn[ax];
+      for (int r = 0; r < NR; ++r) row_at(1 + r)[slot] = c[ax][r];
       __syncthreads();
-      if (out_ok) {
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-          row_store_nt(stage[r * BS + get], co + (size_t)r * Ps, row_n, out_off);
-        row_store_nt(stage[NR * BS + get], xo, row_n, out_off);
-      }
+      // (this workgroup's slots)
+      float* const co = a.coeff_out + (size_t)ax * NR * Ps + i0;
+      float* const xo = a.x_out + (size_t)ax * Ps + i0;
+      write_rows(std::integral_constant<int, NR + 1>{}, 0,
+                 [&](int k) { return k == 0 ? xo : co + (size_t)(k - 1) * Ps; });
       __syncthreads();  // the next component overwrites the stage
     }
   }
@@ -197,17 +317,14 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       for (int e = 0; e < 9; ++e) Fn[e] = 0.0f;
     }
 #pragma unroll
-    for (int e = 0; e < 9; ++e) stage[e * BS + put] = Fn[e];
-    stage[9 * BS + put] = m;
+    for (int e = 0; e < 9; ++e) row_at(e)[slot] = Fn[e];
+    row_at(9)[slot] = m;
     __syncthreads();
-    if (out_ok) {
-      if (a.F_out) {
-#pragma unroll
-        for (int e = 0; e < 9; ++e)
-          row_store_nt(stage[e * BS + get], a.F_out + (size_t)e * Ps + i0, row_n, out_off);
-      }
-      if (a.mass_out) row_store_nt(stage[9 * BS + get], a.mass_out + i0, row_n, out_off);
-    }
+    if (a.F_out)
+      write_rows(std::integral_constant<int, 9>{}, 0,
+                 [&](int k) { return a.F_out + (size_t)k * Ps + i0; });
+    if (a.mass_out)
+      write_rows(std::integral_constant<int, 1>{}, 9, [&](int) { return a.mass_out + i0; });
     __syncthreads();  // the bricks are cleared next
   }
 
@@ -225,84 +342,49 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     }
   }
   if (!valid) m = 0.0f;
-  tile_of[slot] = valid ? brick_tile_id(0, c0, c1, c2) : kNoTile;
-  static_assert(kBrickNodes <= BS, "one brick node per thread");
-  const BrickNode bn = brick_node(tid);
-  if (tid < kBrickNodes) {
+  const int run_slot = run_of[slot];
+  // brick of this slot's run.  A run past kRuns keeps a value of its own (K + run index,
+  // above every distinct-tile index d < kRuns), so that two lanes of different runs never
+  // compare equal below.
+  const bool dedup = n_runs > K;  // (uniform)
+  const int seg = run_slot < 0 || !dedup ? run_slot
+                  : run_slot < kRuns     ? run_brick[run_slot]
+                                         : K + run_slot;
+  const int nb = dedup ? min(n_distinct, K) : n_runs;
+  // this thread's nodes of every brick (it clears and flushes them)
+  constexpr int kOwn = kFuseNodes / BS;
+  static_assert(kOwn * BS == kFuseNodes, "whole nodes per thread");
+  const int own_x = tid & 7, own_y = (tid >> 3) & 7, own_z = tid >> 6;  // z: + q * BS / 64
+  const int own_lds = own_x + kFuseSY * own_y + kFuseSZ * own_z;
+  for (int k = 0; k < nb * kFuseCh; ++k)
 #pragma unroll
-    for (int k = 0; k < kBrickKMAX * 4; ++k) brick[k * kBrickV + bn.lds] = 0.0;
-  }
-  __syncthreads();
-
-  // Bricks are given per distinct tile, not per run: the chunk is in the order of
-  // the previous positions, so a particle that changed cell can split a run of
-  // equal tiles, and per-run segments would then spill the rest of the chunk to
-  // HBM.  Runs of equal tiles in slot order (thread t looks at slot t), then the
-  // first kRuns runs' tiles deduplicated in order of appearance by wavefront 0.
-  constexpr int kRuns = kWave;
-  {
-    const uint64_t tt = tile_of[tid];
-    const bool head = tt != kNoTile && (tid == 0 || tile_of[tid - 1] != tt);
-    const unsigned long long hb = __ballot(head);
-    if (lane == 0) wave_heads[wv] = __popcll(hb);
-    __syncthreads();
-    int pre = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) pre += (w < wv) ? wave_heads[w] : 0;
-    const int run = pre + lanes_below(hb) + (head ? 1 : 0) - 1;
-    seg_of[tid] = run;  // run index for now (-1 before the first valid slot)
-    if (head && run < kRuns) run_tile[run] = tt;
-  }
-  __syncthreads();
-  int nruns = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) nruns += wave_heads[w];
-  const int nr = nruns < kRuns ? nruns : kRuns;
-  if (wv == 0) {
-    const uint64_t mine = lane < nr ? run_tile[lane] : kNoTile;
-    int first_same = lane;  // first run with this run's tile
-    for (int q = nr - 1; q >= 0; --q)
-      if (q < lane && run_tile[q] == mine) first_same = q;
-    const bool first = lane < nr && first_same == lane;
-    const unsigned long long fb = __ballot(first);
-    // distinct index of a first run = first runs before it; a later run takes its
-    // first run's index (all lanes hold a value, so the shuffle is well defined)
-    const int d_first = lanes_below(fb);
-    const int d = __shfl(d_first, first_same, kWave);
-    if (lane < nr) run_brick[lane] = d;
-    if (first && d < kBrickKMAX) seg_tile[d] = mine;
-    if (lane == 0) n_bricks = __popcll(fb);
-  }
-  __syncthreads();
-  const int run_slot = seg_of[slot];
-  // brick of this slot's run; runs past kRuns, and tiles past the brick budget, go to HBM.
-  // A run past kRuns keeps a value of its own (kBrickKMAX + run index, above every
-  // distinct-tile index d < kRuns), so that two lanes of different runs never compare
-  // equal below.
-  const int seg = run_slot < 0 ? -1
-                               : (run_slot < kRuns ? run_brick[run_slot] : kBrickKMAX + run_slot);
-  const int nseg = n_bricks;
+    for (int q = 0; q < kOwn; ++q) brick[k * kFuseV + own_lds + q * (BS / 64) * kFuseSZ] = 0.0;
+  // the new base node in the brick of the old tile, whose first cell is one below the
+  // tile; a slot without a brick, or that moved further, goes to HBM
+  const uint32_t tl = tile_bits(cell_of[slot]);
+  const int w0 = (int)(tl & 1023u) - 1, w1 = (int)((tl >> 10) & 1023u) - 1,
+            w2 = (int)((tl >> 20) & 1023u) - 1;
+  const bool lds = gather && seg >= 0 && seg < K && (unsigned)(c0 - w0) < (unsigned)kBrickN &&
+                   (unsigned)(c1 - w1) < (unsigned)kBrickN &&
+                   (unsigned)(c2 - w2) < (unsigned)kBrickN;
   if (a.regions) {
-    // the regions the scatter lands in: each brick's 6^3 nodes, and the 6^3 nodes of
-    // the tile of every slot that went to HBM directly (a box holding its stencil);
-    // from the run bookkeeping, before the scatter holds its node values (plain stores)
-    const int nb = nseg < kBrickKMAX ? nseg : kBrickKMAX;
+    // the regions the scatter lands in: the 6^3 nodes of each brick's tile, and those of
+    // the new tile of every slot that left its tile or went to HBM (a box holding its
+    // stencil); before the scatter holds its node values (plain stores)
     if (tid < 8 * nb) {
-      const uint32_t tc = (uint32_t)seg_tile[tid >> 3];
+      const uint32_t tc = run_tile[tid >> 3];
       flag_box_corner(a.regions, g.region_off, (uint32_t)ck.s, nx, ny, nz,
-                      (int)(tc & 1023u) * kBrickT, (int)((tc >> 10) & 1023u) * kBrickT,
-                      (int)(tc >> 20) * kBrickT, kBrickN, tid & 7);
+                      (int)(tc & 1023u), (int)((tc >> 10) & 1023u),
+                      (int)(tc >> 20), kBrickN, tid & 7);
     }
-    const int run_t = seg_of[tid];
-    if (run_t >= 0 && (run_t >= kRuns || run_brick[run_t] >= kBrickKMAX)) {
-      const uint32_t tc = (uint32_t)tile_of[tid];
+    if (valid && (!lds || tile_bits((uint32_t)c0 | ((uint32_t)c1 << 10) | ((uint32_t)c2 << 20)) != tl)) {
 #pragma unroll
       for (int corner = 0; corner < 8; ++corner)
-        flag_box_corner(a.regions, g.region_off, (uint32_t)ck.s, nx, ny, nz,
-                        (int)(tc & 1023u) * kBrickT, (int)((tc >> 10) & 1023u) * kBrickT,
-                        (int)(tc >> 20) * kBrickT, kBrickN, corner);
+        flag_box_corner(a.regions, g.region_off, (uint32_t)ck.s, nx, ny, nz, c0 & ~(kBrickT - 1),
+                        c1 & ~(kBrickT - 1), c2 & ~(kBrickT - 1), kBrickN, corner);
     }
   }
+  __syncthreads();  // the bricks are clear
   // the lane pair (lane ^ 1), and with quads the other pair of the quad, share this
   // lane's segment and base node: every lane runs the exchanges (an invalid one with
   // zero mass), since a DPP read from a lane that did not execute it is undefined
@@ -310,7 +392,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   const int pair_key = pair_swap_i(mykey), pair_seg = pair_swap_i(seg);
   const bool pair = mykey == pair_key && seg == pair_seg;
   bool quad = false;
-  if constexpr (LG == 2) {
+  if (quads) {
     const int quad_pair = quad_swap_i((int)pair), quad_key = quad_swap_i(mykey);
     const int quad_seg = quad_swap_i(seg);
     quad = pair && quad_pair != 0 && mykey == quad_key && seg == quad_seg;
@@ -322,14 +404,13 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     const Rows Rx = p2g_rows_scaled(basis_p2g(u0), m);
     const Rows Ry = p2g_rows_scaled(basis_p2g(u1), 1.0f);
     const Rows Rz = p2g_rows_scaled(basis_p2g(u2), 1.0f);
-    const bool lds = seg < kBrickKMAX;
-    const int lbase = (c0 & 3) + kBrickSY * (c1 & 3) + kBrickSZ * (c2 & 3);
+    const int lbase = (c0 - w0) + kFuseSY * (c1 - w1) + kFuseSZ * (c2 - w2);
     const int64_t gbase = g.node_off + (int64_t)(c2 * ny + c1) * nx + c0;
-    double* const lb = brick + (lds ? max(seg, 0) : 0) * 4 * kBrickV + lbase;
+    double* const lb = brick + (lds ? seg * kFuseCh * kFuseV + lbase : 0);
     // one plane of 9 node values at a time: the folds run on every lane, then a
     // single predicated block per plane does the atomics
     auto emitter = [&](int ch) {
-      double* const lbc = lb + ch * kBrickV;
+      double* const lbc = lb + (ch % kFuseCh) * kFuseV;
       // (the HBM base is formed only on that rare path, to keep registers free)
       float* const gc = ch == 0 ? a.gm : ch == 1 ? a.gp0 : ch == 2 ? a.gp1 : a.gp2;
       return [=](int jz, float (&v)[9]) {
@@ -337,7 +418,10 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
           w[k] = pair_fold(v[k], pair_f);
-          if constexpr (LG == 2) w[k] = quad_fold(w[k], quad_f);
+        }
+        if (quads) {
+#pragma unroll
+          for (int k = 0; k < 9; ++k) w[k] = quad_fold(w[k], quad_f);
         }
         if (!emit) return;
         if (lds) {
@@ -345,7 +429,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
           for (int jy = 0; jy < 3; ++jy)
 #pragma unroll
             for (int jx = 0; jx < 3; ++jx)
-              atomicAdd(lbc + jx + kBrickSY * jy + kBrickSZ * jz, (double)w[jx + 3 * jy]);
+              atomicAdd(lbc + jx + kFuseSY * jy + kFuseSZ * jz, (double)w[jx + 3 * jy]);
         } else {
 #pragma unroll
           for (int jy = 0; jy < 3; ++jy)
@@ -355,6 +439,35 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
         }
       };
     };
+    // Flush of a round: one global float atomic per channel per non-zero brick node, by
+    // the node's owner thread, which clears it for the next round.
+    auto flush = [&](int ch0, bool clear) {
+      float* const dst[4] = {a.gm, a.gp0, a.gp1, a.gp2};
+      for (int sb = 0; sb < nb; ++sb) {
+        const uint32_t tc = run_tile[sb];
+        const int gx = (int)(tc & 1023u) - 1 + own_x;
+        const int gy = (int)((tc >> 10) & 1023u) - 1 + own_y;
+        const int gz0 = (int)(tc >> 20) - 1 + own_z;
+        if ((unsigned)gx >= (unsigned)nx || (unsigned)gy >= (unsigned)ny) continue;
+        const int64_t node0 = g.node_off + ((int64_t)(gz0 * ny + gy) * nx + gx);
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) {
+          double* const src = brick + sb * kFuseCh * kFuseV + own_lds + q * (BS / 64) * kFuseSZ;
+          if ((unsigned)(gz0 + q * (BS / 64)) >= (unsigned)nz) continue;
+          const int64_t node = node0 + q * (BS / 64) * (int64_t)nxny;
+          float v[kFuseCh];
+#pragma unroll
+          for (int k = 0; k < kFuseCh; ++k) v[k] = (float)src[k * kFuseV];
+          if (clear) {
+#pragma unroll
+            for (int k = 0; k < kFuseCh; ++k) src[k * kFuseV] = 0.0;
+          }
+#pragma unroll
+          for (int k = 0; k < kFuseCh; ++k)
+            if (v[k] != 0.0f) atomicAdd(dst[ch0 + k] + node, v[k]);
+        }
+      }
+    };
     {  // mass: m W_ip
       float one[27];
 #pragma unroll
@@ -362,41 +475,35 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       stream_modes_planes<1>(one, Rx, Ry, Rz, emitter(0));
     }
     stream_modes_planes<NR>(c[0], Rx, Ry, Rz, emitter(1));
-    stream_modes_planes<NR>(c[1], Rx, Ry, Rz, emitter(2));
-    stream_modes_planes<NR>(c[2], Rx, Ry, Rz, emitter(3));
-  }
-  __syncthreads();
-
-  // flush: one global float atomic per channel per non-zero brick node, by the
-  // node's owner thread
-  const int nb = nseg < kBrickKMAX ? nseg : kBrickKMAX;
-
-  if (tid < kBrickNodes) {
-    for (int sb = 0; sb < nb; ++sb) {
-      const uint32_t tc = (uint32_t)seg_tile[sb];
-      const int gx = (int)(tc & 1023u) * kBrickT + bn.lx;
-      const int gy = (int)((tc >> 10) & 1023u) * kBrickT + bn.ly;
-      const int gz = (int)(tc >> 20) * kBrickT + bn.lz;
-      if (gx >= nx || gy >= ny || gz >= nz) continue;
-      const int64_t node = g.node_off + ((int64_t)(gz * ny + gy) * nx + gx);
-      const double* const src = brick + sb * 4 * kBrickV + bn.lds;
-      float* const dst[4] = {a.gm, a.gp0, a.gp1, a.gp2};
-#pragma unroll
-      for (int ch = 0; ch < 4; ++ch) {
-        const float v = (float)src[ch * kBrickV];
-        if (v != 0.0f) atomicAdd(dst[ch] + node, v);
-      }
+    if constexpr (kFuseCh == 2) {
+      __syncthreads();
+      flush(0, true);
+      __syncthreads();
     }
+    stream_modes_planes<NR>(c[1], Rx, Ry, Rz, emitter(2));
+#pragma unroll
+    for (int r = NR - kKept; r < NR; ++r) c[2][r] = row_at(1 + r)[slot];  // (this thread's own)
+    stream_modes_planes<NR>(c[2], Rx, Ry, Rz, emitter(3));
+    __syncthreads();
+    flush(4 - kFuseCh, false);
   }
 }
 
 template <int NR, class Scenes>
 hipError_t launch_nr(const G2P2GArgs& a, const Scenes& sc, unsigned blocks, hipStream_t stream) {
   constexpr int BS = kSceneChunk;
-  if (a.lane_group == 4)
-    g2p2g_kernel<NR, BS, Scenes, 2><<<blocks, BS, 0, stream>>>(a, sc);
-  else
-    g2p2g_kernel<NR, BS, Scenes, 1><<<blocks, BS, 0, stream>>>(a, sc);
+  // Whole lines cost more instructions per row than a slot per thread, and pay at 27 modes
+  // when the rows start off the 32-byte sectors (measured, 4.19 M particles, a slot per
+  // thread and whole lines: P odd 493 and 439 us, P = 4 mod 8 454 and 440, P = 8 mod 16 407
+  // and 417; at 4 modes, P odd, 255 and 283).  A batch's workgroups neighbour each other on
+  // one XCD, whose L2 joins the parts of a line: 718 us a slot per thread, 745 in lines.
+  if constexpr (NR > 8 && std::is_same_v<Scenes, OneScene>) {
+    if (!rows_on_sectors(a.P, {a.coeff_out, a.x_out})) {
+      g2p2g_kernel<NR, BS, Scenes, true><<<blocks, BS, 0, stream>>>(a, sc);
+      return hipGetLastError();
+    }
+  }
+  g2p2g_kernel<NR, BS, Scenes, false><<<blocks, BS, 0, stream>>>(a, sc);
   return hipGetLastError();
 }
 

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "polypic_device.hpp"
 #include "polypic_scene.hpp"
 
@@ -18,6 +20,13 @@ constexpr int kComputeUnits = 256;  // MI355X
 // (grids are at most 1026^3 nodes: the count fits 32 bits)
 inline unsigned node_blocks(int nx, int ny, int nz) {
   return (unsigned)(((int64_t)nx * ny * nz + 255) / 256);
+}
+
+// Do rows of P floats at these bases (null ones aside) all start on 32-byte sectors?
+inline bool rows_on_sectors(int64_t P, std::initializer_list<const void*> bases) {
+  uintptr_t low = (uintptr_t)P * sizeof(float);
+  for (const void* b : bases) low |= (uintptr_t)b;
+  return low % 32 == 0;
 }
 
 // active regions of an nx x ny x nz grid
@@ -161,7 +170,7 @@ struct G2P2GArgs {
   float* gp2;
   int32_t* status;
   int64_t gstride;       // channel stride of gv
-  int lane_group;        // particles folded per brick atomic: 2 (default) or 4
+  int lane_group;        // particles folded per brick atomic: 2 or 4, 0: by the chunk's cells
   int accumulate;        // 1: add to the grid as it is (the caller cleared it)
   int sched;             // chunk order: kSchedLinear or kSchedXcd
   uint32_t* regions;     // region flags to set where the scatter lands (or nullptr)
