@@ -81,8 +81,20 @@ __host__ __device__ constexpr bool has_mode(int kx, int ky, int kz) {
 // outside [0, n - 3] (or the position is not finite).
 __device__ __forceinline__ bool stencil_axis(float x, float o, float inv_dx, int n, int& b,
                                              float& t) {
-  // (the product must not be contracted into either subtraction, which the rounding
-  // intrinsics alone do not keep the compiler from: b and t would differ between kernels)
+  const float u = __fmul_rn(__fsub_rn(x, o), inv_dx);
+  const float f = floorf(__fsub_rn(u, 0.5f));
+  const bool ok = (f >= 0.0f) && (f <= (float)(n - 3));
+  b = ok ? (int)f : 0;
+  t = ok ? __fsub_rn(u, f + 1.0f) : 0.0f;
+  return ok;
+}
+
+// The same with the product kept from contraction into either subtraction, which the
+// rounding intrinsics alone do not keep the compiler from: for a kernel that computes the
+// offsets of one particle in several places, which must agree to the bit.  (The cell keys
+// keep the form above: their roundings decide ties at cell boundaries.)
+__device__ __forceinline__ bool stencil_axis_apart(float x, float o, float inv_dx, int n, int& b,
+                                                   float& t) {
 #pragma clang fp contract(off)
   const float d = x - o;
   const float u = d * inv_dx;

@@ -136,9 +136,9 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   }
   int b0, b1, b2;
   float t0, t1, t2;
-  bool ok = stencil_axis(xp[0], g.ox, g.inv_dx, nx, b0, t0);
-  ok &= stencil_axis(xp[1], g.oy, g.inv_dx, ny, b1, t1);
-  ok &= stencil_axis(xp[2], g.oz, g.inv_dx, nz, b2, t2);
+  bool ok = stencil_axis_apart(xp[0], g.ox, g.inv_dx, nx, b0, t0);
+  ok &= stencil_axis_apart(xp[1], g.oy, g.inv_dx, ny, b1, t1);
+  ok &= stencil_axis_apart(xp[2], g.oz, g.inv_dx, nz, b2, t2);
   if (in && !ok) raise_flag(a.status, kFlagRange);
   bool gather = in && ok;
   cell_of[slot] = gather ? (uint32_t)b0 | ((uint32_t)b1 << 10) | ((uint32_t)b2 << 20) : kNoCell;
@@ -199,9 +199,9 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     xp[2] = stage[2 * BS + slot];
     p = __float_as_int(stage[3 * BS + slot]);
     gather = cell_of[slot] != kNoCell;
-    stencil_axis(xp[0], g.ox, g.inv_dx, nx, b0, t0);
-    stencil_axis(xp[1], g.oy, g.inv_dx, ny, b1, t1);
-    stencil_axis(xp[2], g.oz, g.inv_dx, nz, b2, t2);
+    stencil_axis_apart(xp[0], g.ox, g.inv_dx, nx, b0, t0);
+    stencil_axis_apart(xp[1], g.oy, g.inv_dx, ny, b1, t1);
+    stencil_axis_apart(xp[2], g.oz, g.inv_dx, nz, b2, t2);
     vbase = g.node_off + (int64_t)(b2 * ny + b1) * nx + b0;
     gather_nodes(0, v);
     __syncthreads();  // the stage is read
@@ -333,9 +333,9 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   int c0 = 0, c1 = 0, c2 = 0;
   float u0 = 0.f, u1 = 0.f, u2 = 0.f;
   if (valid) {
-    bool ok2 = stencil_axis(xn[0], g.ox, g.inv_dx, nx, c0, u0);
-    ok2 &= stencil_axis(xn[1], g.oy, g.inv_dx, ny, c1, u1);
-    ok2 &= stencil_axis(xn[2], g.oz, g.inv_dx, nz, c2, u2);
+    bool ok2 = stencil_axis_apart(xn[0], g.ox, g.inv_dx, nx, c0, u0);
+    ok2 &= stencil_axis_apart(xn[1], g.oy, g.inv_dx, ny, c1, u1);
+    ok2 &= stencil_axis_apart(xn[2], g.oz, g.inv_dx, nz, c2, u2);
     if (!ok2) {  // (x' is clamped into the grid: only for a grid too small for a stencil)
       raise_flag(a.status, kFlagRange);
       valid = false;

@@ -42,17 +42,15 @@ constexpr int kMacBS = 256;
 // stencil of the lattice shifted by +dx/2 (bs, ts); false if either leaves [0, n - 3].
 __device__ __forceinline__ bool face_axes(float x, float o, float inv_dx, int n, int& b, float& t,
                                           int& bs, float& ts) {
-#pragma clang fp contract(off)
-  const float d = x - o;
-  const float u = d * inv_dx;
-  const float f = floorf(u - 0.5f);
-  const float us = u - 0.5f;  // exact for u < 2^22
-  const float fs = floorf(us - 0.5f);
+  const float u = __fmul_rn(__fsub_rn(x, o), inv_dx);
+  const float f = floorf(__fsub_rn(u, 0.5f));
+  const float us = __fsub_rn(u, 0.5f);  // exact for u < 2^22
+  const float fs = floorf(__fsub_rn(us, 0.5f));
   const bool ok = (f >= 0.0f) && (f <= (float)(n - 3)) && (fs >= 0.0f) && (fs <= (float)(n - 3));
   b = ok ? (int)f : 0;
-  t = ok ? u - (f + 1.0f) : 0.0f;
+  t = ok ? __fsub_rn(u, f + 1.0f) : 0.0f;
   bs = ok ? (int)fs : 0;
-  ts = ok ? us - (fs + 1.0f) : 0.0f;
+  ts = ok ? __fsub_rn(us, fs + 1.0f) : 0.0f;
   return ok;
 }
 
