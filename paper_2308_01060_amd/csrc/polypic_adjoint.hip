@@ -63,10 +63,19 @@ __global__ __launch_bounds__(256) void grid_update_backward_kernel(GridUpdateBac
 }
 
 // ---------------------------------------------------------------- P2G adjoint (gather)
-template <int NR>
+// kLines (no permutation): the gradient rows are staged in LDS and written in whole lines
+// (rows_out_lines).
+template <int NR, bool kLines>
 __global__ __launch_bounds__(256) void p2g_backward_kernel(P2GBackArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.P) return;
+  constexpr int BS = 256, NW = BS / kWave;
+  __shared__ alignas(16) float stage[kLines ? NR * BS : 1];
+  const int tid = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * BS;
+  const int n_slots = (int)min((int64_t)BS, a.P - i0);
+  // (a thread past the slots repeats the last one and writes nothing)
+  const bool in = tid < n_slots;
+  if (!kLines && !in) return;
+  const int64_t i = i0 + min(tid, n_slots - 1);
   const size_t Ps = (size_t)a.P;
   const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
   const int p = a.perm ? min(max(a.perm[i], 0), (int)(a.P - 1)) : (int)i;
@@ -77,13 +86,16 @@ __global__ __launch_bounds__(256) void p2g_backward_kernel(P2GBackArgs a) {
   ok &= stencil_axis(a.x[2 * Ps + p], a.g.oz, a.g.inv_dx, nz, b2, t2);
   if (!ok) {
     // skipped in the forward pass: no gradient
-    raise_flag(a.status, kFlagRange);
+    if (in) raise_flag(a.status, kFlagRange);
+    if (!kLines) {
 #pragma unroll
-    for (int ax = 0; ax < 3; ++ax)
+      for (int ax = 0; ax < 3; ++ax)
 #pragma unroll
-      for (int r = 0; r < NR; ++r) a.coeff_grad[((size_t)ax * NR + r) * Ps + p] = 0.0f;
-    if (a.mass_grad) a.mass_grad[p] = 0.0f;
-    return;
+        for (int r = 0; r < NR; ++r) a.coeff_grad[((size_t)ax * NR + r) * Ps + p] = 0.0f;
+      if (a.mass_grad) a.mass_grad[p] = 0.0f;
+      return;
+    }
+    // (staged: the thread goes on, at the nodes its base gives, for the barriers' sake)
   }
   Rows R[3], dR[3];
   p2g_rows(t0, R[0], dR[0]);
@@ -179,17 +191,33 @@ __global__ __launch_bounds__(256) void p2g_backward_kernel(P2GBackArgs a) {
               fmaf(R[2].r[kz][2], By[2], fmaf(R[2].r[kz][1], By[1], R[2].r[kz][0] * By[0]));
           const float Tx =
               fmaf(R[2].r[kz][2], Bx[2], fmaf(R[2].r[kz][1], Bx[1], R[2].r[kz][0] * Bx[0]));
-          __builtin_nontemporal_store(m * T, cg + (size_t)r * Ps);
+          if constexpr (kLines)
+            stage[r * BS + tid] = ok ? m * T : 0.0f;
+          else
+            __builtin_nontemporal_store(m * T, cg + (size_t)r * Ps);
           mg = fmaf(cr, T, mg);
           sx = fmaf(cr, Tx, sx);
           sy = fmaf(cr, Ty, sy);
           sz = fmaf(cr, Tz, sz);
         }
+        // (pins the sums here: they do not depend on the rows, and the compiler otherwise
+        // sinks them past the barrier with every plane's stages live, 227 registers)
+        if constexpr (kLines) asm volatile("" : "+v"(sx), "+v"(sy), "+v"(sz), "+v"(mg));
       }
     }
     xg[0] = fmaf(m, sx, xg[0]);
     xg[1] = fmaf(m, sy, xg[1]);
     xg[2] = fmaf(m, sz, xg[2]);
+    if constexpr (kLines) {
+      __syncthreads();
+      float* const rows = a.coeff_grad + (size_t)ax * NR * Ps + i0;
+      rows_out_lines<NW, NR>(stage, n_slots, tid, [&](int k) { return rows + (size_t)k * Ps; });
+      __syncthreads();  // the next component overwrites the stage
+    }
+  }
+  if (kLines && (!in || !ok)) {
+    if (in && a.mass_grad) a.mass_grad[p] = 0.0f;
+    return;
   }
   const float inv_dx = a.g.inv_dx;
   a.x_grad[p] += inv_dx * xg[0];
@@ -398,7 +426,15 @@ __global__ __launch_bounds__(BS) void g2p_backward_kernel(G2PBackArgs a) {
 
 template <int NR>
 hipError_t launch_p2g_back_nr(const P2GBackArgs& a, hipStream_t s) {
-  p2g_backward_kernel<NR><<<(unsigned)((a.P + 255) / 256), 256, 0, s>>>(a);
+  const unsigned blocks = (unsigned)((a.P + 255) / 256);
+  if constexpr (NR == 27) {
+    // (measured, a call: 366 -> 273 us at P = 1769471, 260 -> 190 at 1200007; 225 at 1769472)
+    if (!a.perm && rows_want_lines(NR, 64, a.P, {a.coeff_grad})) {
+      p2g_backward_kernel<NR, true><<<blocks, 256, 0, s>>>(a);
+      return hipGetLastError();
+    }
+  }
+  p2g_backward_kernel<NR, false><<<blocks, 256, 0, s>>>(a);
   return hipGetLastError();
 }
 

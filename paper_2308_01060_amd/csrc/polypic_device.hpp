@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace polypic {
 
 constexpr int kWave = 64;
@@ -768,15 +770,16 @@ __device__ __forceinline__ float row_load(const float* row, int n, int lane_byte
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row_rsrc(row, n), lane_byte_off, 0, 0));
 }
 
-// Staged rows out in whole lines, wherever the rows start: a wavefront writes n slots (n up
-// to 4 * kWave) of a row, in LDS in slot order, to row[0, n).  Body: whole 128-byte lines
+// Staged rows out in whole lines, wherever the rows start: the n slots of a workgroup's
+// slice of a row, in LDS in slot order, to row[0, n).  Body: whole 128-byte lines
 // (rows_body(n) slots, the same for every row) from the row's first line boundary on, four
 // slots per lane, streamed past the caches.  Ends: the up to 63 slots before and after the
-// body, one per lane.  Rows of P floats start on 64-byte boundaries only when 16 divides P;
+// body, one per lane, through the caches, where a neighbouring workgroup's part of the line
+// can join them.  Rows of P floats start on 64-byte boundaries only when 16 divides P;
 // written slot by lane, a wavefront's 256 bytes otherwise split 64-byte sectors with its
 // neighbours', and each part goes to memory by itself (measured, 84 rows of 4.0 M floats:
 // 251 us slot by lane when 32 divides P, 310 at 16, 495 at 8 and 580 at an odd P; in whole
-// lines 229 to 260 at any).
+// lines 229 to 260 at any; with the ends streamed as well 423 at an odd P).
 constexpr int kLine = 32;  // floats
 typedef float Float4 __attribute__((ext_vector_type(4)));
 
@@ -785,9 +788,9 @@ __device__ __forceinline__ int rows_body(int n) { return max(n - (kLine - 1), 0)
 __device__ __forceinline__ int row_head(const float* row) {
   return (int)(-(uint32_t)((uintptr_t)row >> 2) & (kLine - 1));
 }
-// lanes with 4 * lane < rows_body(n) call it
-__device__ __forceinline__ void row_store_body(const float* staged, float* row, int lane) {
-  const int at = row_head(row) + 4 * lane;
+// the quad'th four slots of the body (4 * quad < rows_body(n))
+__device__ __forceinline__ void row_store_body(const float* staged, float* row, int quad) {
+  const int at = row_head(row) + 4 * quad;
   const float* const s = staged + at;
   __builtin_nontemporal_store(Float4{s[0], s[1], s[2], s[3]},
                               reinterpret_cast<Float4*>(row + at));
@@ -795,7 +798,30 @@ __device__ __forceinline__ void row_store_body(const float* staged, float* row, 
 __device__ __forceinline__ void row_store_ends(const float* staged, float* row, int n, int body,
                                                int lane) {
   const int at = min(lane + (lane < row_head(row) ? 0 : body), n);  // (n: dropped)
-  row_store_nt(staged[min(at, n - 1)], row, n, at * (int)sizeof(float));
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(staged[min(at, n - 1)]), row_rsrc(row, n),
+                                        at * (int)sizeof(float), 0, 0);
+}
+// ROWS rows of a workgroup of NW wavefronts, row k from staged + k * NW * kWave to dst(k); a
+// wavefront takes 4 * kWave slots of a row at a time.  (Bodies first: they are free of
+// branches among themselves.)
+template <int NW, int ROWS, class Dst>
+__device__ __forceinline__ void rows_out_lines(const float* staged, int n, int tid, Dst&& dst) {
+  static_assert(NW % 4 == 0, "whole segments of 4 * kWave slots");
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int body = rows_body(n);  // (uniform)
+  auto each = [&](int first, auto step, auto&& put) {
+#pragma unroll
+    for (int k = 0; k < ROWS; k += step)
+      if (k + step <= ROWS || k + first < ROWS)
+        put(staged + (k + first) * NW * kWave, dst(k + first));
+  };
+  const int quad = lane + wave / 4 * kWave;  // this lane's four slots
+  if (4 * quad < body)
+    each(wave % 4, std::integral_constant<int, 4>{},
+         [&](const float* s, float* row) { row_store_body(s, row, quad); });
+  each(wave, std::integral_constant<int, NW>{},
+       [&](const float* s, float* row) { row_store_ends(s, row, n, body, lane); });
 }
 
 // popcount of the bits of `mask` below this lane

@@ -13,12 +13,20 @@ namespace polypic {
 
 namespace {
 
-template <int NR, int BS, class Scenes>
+// kLines: the rows are staged in LDS and written in whole lines (rows_out_lines).
+template <int NR, int BS, class Scenes, bool kLines>
 __global__ __launch_bounds__(BS) void g2p_kernel(G2PArgs a, Scenes sc) {
+  constexpr int NW = BS / kWave;
+  constexpr int kRows = NR + 1 > 9 ? NR + 1 : 9;  // a component, or F
+  __shared__ alignas(16) float stage[kLines ? kRows * BS : 1];
   const ChunkRange cr = block_chunks(a.sched, (a.P + BS - 1) / BS);  // one chunk
   const int64_t i0 = cr.begin * BS;
-  const int64_t i = i0 + threadIdx.x;
-  if (i >= a.P) return;
+  const int tid = threadIdx.x;
+  const int n_slots = (int)min((int64_t)BS, a.P - i0);
+  // (a thread past the slots repeats the last one and writes nothing)
+  const bool in = tid < n_slots;
+  if (!kLines && !in) return;
+  const int64_t i = i0 + min(tid, n_slots - 1);
   const int s0 = sc.first(i0);  // uniform over the workgroup
   const int s = sc.of(i, s0);
   // one wave-uniform lookup unless the wavefront straddles a scene boundary
@@ -36,7 +44,7 @@ __global__ __launch_bounds__(BS) void g2p_kernel(G2PArgs a, Scenes sc) {
   bool ok = stencil_axis(xp[0], sg.ox, sg.inv_dx, nx, b0, t0);
   ok &= stencil_axis(xp[1], sg.oy, sg.inv_dx, ny, b1, t1);
   ok &= stencil_axis(xp[2], sg.oz, sg.inv_dx, sg.nz, b2, t2);
-  if (!ok) raise_flag(a.status, kFlagRange);
+  if (in && !ok) raise_flag(a.status, kFlagRange);
 
   const Proj1D px = proj_g2p(t0);
   const Proj1D py = proj_g2p(t1);
@@ -71,14 +79,25 @@ __global__ __launch_bounds__(BS) void g2p_kernel(G2PArgs a, Scenes sc) {
     // Outputs are streamed with non-temporal stores: written once, never re-read by this
     // kernel, they would otherwise displace the grid lines the gathers reuse from L2
     // (measured: 0.40 -> 0.27 ms at 27 modes, 4.19 M particles).
-    float* co = a.coeff_out + (size_t)ax * NR * Ps + i;
+    float xn = fmaf(a.dt, c[0], xp[ax]);
+    xn = fmaxf(xn, sg.lo[ax]);
+    xn = fminf(xn, sg.hi[ax]);
+    if constexpr (kLines) {
+      float* const row = stage + tid;
+      row[0] = xn;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) __builtin_nontemporal_store(c[r], co + (size_t)r * Ps);
-    if (a.x_out) {
-      float xn = fmaf(a.dt, c[0], xp[ax]);
-      xn = fmaxf(xn, sg.lo[ax]);
-      xn = fminf(xn, sg.hi[ax]);
-      __builtin_nontemporal_store(xn, a.x_out + (size_t)ax * Ps + i);
+      for (int r = 0; r < NR; ++r) row[(1 + r) * BS] = c[r];
+      __syncthreads();
+      float* const co = a.coeff_out + (size_t)ax * NR * Ps + i0;
+      rows_out_lines<NW, NR>(stage + BS, n_slots, tid, [&](int k) { return co + (size_t)k * Ps; });
+      if (a.x_out)
+        rows_out_lines<NW, 1>(stage, n_slots, tid, [&](int) { return a.x_out + (size_t)ax * Ps + i0; });
+      __syncthreads();  // the next component overwrites the stage
+    } else {
+      float* co = a.coeff_out + (size_t)ax * NR * Ps + i;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) __builtin_nontemporal_store(c[r], co + (size_t)r * Ps);
+      if (a.x_out) __builtin_nontemporal_store(xn, a.x_out + (size_t)ax * Ps + i);
     }
 #pragma unroll
     for (int b = 0; b < 3; ++b) lin[ax][b] = (NR >= 4) ? c[1 + b] : 0.0f;
@@ -93,21 +112,40 @@ __global__ __launch_bounds__(BS) void g2p_kernel(G2PArgs a, Scenes sc) {
         float acc = 0.0f;
 #pragma unroll
         for (int k = 0; k < 3; ++k) acc = fmaf(lin[r][k], F[3 * k + col], acc);
-        __builtin_nontemporal_store(fmaf(s, acc, F[3 * r + col]),
-                                     a.F_out + (size_t)(3 * r + col) * Ps + i);
+        const float f = fmaf(s, acc, F[3 * r + col]);
+        if constexpr (kLines)
+          stage[(3 * r + col) * BS + tid] = f;
+        else
+          __builtin_nontemporal_store(f, a.F_out + (size_t)(3 * r + col) * Ps + i);
       }
+    if constexpr (kLines) {
+      __syncthreads();
+      rows_out_lines<NW, 9>(stage, n_slots, tid,
+                            [&](int k) { return a.F_out + (size_t)k * Ps + i0; });
+    }
   }
+  if (!in) return;
   if (a.mass_out) __builtin_nontemporal_store(a.mass_in[p], a.mass_out + i);
 }
 
 template <int NR, class Scenes>
 hipError_t launch_nr(const G2PArgs& a, const Scenes& sc, hipStream_t stream) {
+  if constexpr (NR == 27) {
+    // (measured, 27 modes: 229 -> 115 us at P = 1500003, 110 at 1500032; 512 threads against
+    // 256: 128 and 138 at 1769471)
+    if (rows_want_lines(NR, 64, a.P, {a.coeff_out, a.x_out})) {
+      constexpr int BS = 512;
+      const unsigned blocks = (unsigned)((a.P + BS - 1) / BS);
+      g2p_kernel<NR, BS, Scenes, true><<<blocks, BS, 0, stream>>>(a, sc);
+      return hipGetLastError();
+    }
+  }
   // 512 particles per workgroup: each output row is then written in 2 KB runs per
   // workgroup (measured in the step, 27 modes, 4.19 M particles: 0.37 ms at 256
   // threads, 0.27 ms at 512, 0.32 ms at 1024)
   constexpr int BS = 512;
   const unsigned blocks = (unsigned)((a.P + BS - 1) / BS);
-  g2p_kernel<NR, BS, Scenes><<<blocks, BS, 0, stream>>>(a, sc);
+  g2p_kernel<NR, BS, Scenes, false><<<blocks, BS, 0, stream>>>(a, sc);
   return hipGetLastError();
 }
 

@@ -239,22 +239,15 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   // rows lie past the bricks.
   auto row_at = [&](int k) { return stage + k * BS; };
   // `rows` staged rows out, row k from row_at(k0 + k) to dst(k): every thread its slot, or
-  // (kLines) in whole lines, a quarter of the rows per wavefront
-  const int wave = __builtin_amdgcn_readfirstlane(wv);
+  // in whole lines
   auto write_rows = [&](auto rows, int k0, auto dst) {
-    if constexpr (!kLines) {
+    if constexpr (kLines) {
+      static_assert(BS == 4 * kWave, "rows of 4 slots per lane");
+      rows_out_lines<NW, rows>(row_at(k0), n_slots, tid, dst);
+    } else {
 #pragma unroll
       for (int k = 0; k < rows; ++k)
         row_store_nt(row_at(k0 + k)[tid], dst(k), n_slots, tid * (int)sizeof(float));
-    } else {
-      const int body = rows_body(n_slots);  // (uniform)
-      auto each = [&](auto&& put) {
-#pragma unroll
-        for (int k = 0; k < rows; k += NW)
-          if (k + NW <= rows || k + wave < rows) put(row_at(k0 + k + wave), dst(k + wave));
-      };
-      if (4 * lane < body) each([&](const float* s, float* row) { row_store_body(s, row, lane); });
-      each([&](const float* s, float* row) { row_store_ends(s, row, n_slots, body, lane); });
     }
   };
   {
@@ -493,12 +486,13 @@ template <int NR, class Scenes>
 hipError_t launch_nr(const G2P2GArgs& a, const Scenes& sc, unsigned blocks, hipStream_t stream) {
   constexpr int BS = kSceneChunk;
   // Whole lines cost more instructions per row than a slot per thread, and pay at 27 modes
-  // when the rows start off the 32-byte sectors (measured, 4.19 M particles, a slot per
-  // thread and whole lines: P odd 493 and 439 us, P = 4 mod 8 454 and 440, P = 8 mod 16 407
-  // and 417; at 4 modes, P odd, 255 and 283).  A batch's workgroups neighbour each other on
-  // one XCD, whose L2 joins the parts of a line: 718 us a slot per thread, 745 in lines.
+  // when the rows start off the 32-byte sectors (measured, a slot per thread and whole
+  // lines: P = 2500007 309 and 251 us, 4194303 493 and 488; P = 2500008 260 and 265,
+  // 4000040 406 and 450; at 4 modes, P = 2500007, 153 and 168).  A batch's workgroups
+  // neighbour each other on one XCD, whose L2 joins the parts of a line: 718 us a slot per
+  // thread, 745 in lines.
   if constexpr (NR > 8 && std::is_same_v<Scenes, OneScene>) {
-    if (!rows_on_sectors(a.P, {a.coeff_out, a.x_out})) {
+    if (rows_want_lines(NR, 32, a.P, {a.coeff_out, a.x_out})) {
       g2p2g_kernel<NR, BS, Scenes, true><<<blocks, BS, 0, stream>>>(a, sc);
       return hipGetLastError();
     }

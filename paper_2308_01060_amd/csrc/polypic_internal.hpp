@@ -22,11 +22,18 @@ inline unsigned node_blocks(int nx, int ny, int nz) {
   return (unsigned)(((int64_t)nx * ny * nz + 255) / 256);
 }
 
-// Do rows of P floats at these bases (null ones aside) all start on 32-byte sectors?
-inline bool rows_on_sectors(int64_t P, std::initializer_list<const void*> bases) {
+// Should a kernel write its 81 rows of P floats (27 modes; null bases aside) in whole lines
+// (rows_out_lines)?  Where some row starts off the `sector` bytes that a wavefront's stores
+// may share with a neighbour's at no cost, and the rows are more than the last-level cache
+// joins by itself (48 MB; measured, slot by lane and whole lines, staggered G2P: 12.4 and
+// 12.6 us at 100,003 particles, 28.0 and 18.3 at 200,003; P2G adjoint, 4 calls: 91 and 97,
+// 187 and 170).  With 8 modes or fewer the lines' instructions cost what they save.
+inline bool rows_want_lines(int n_modes, int sector, int64_t P,
+                            std::initializer_list<const void*> bases) {
+  if (n_modes < 27 || P * 12 * n_modes <= (int64_t)48 << 20) return false;
   uintptr_t low = (uintptr_t)P * sizeof(float);
   for (const void* b : bases) low |= (uintptr_t)b;
-  return low % 32 == 0;
+  return low % (uintptr_t)sector != 0;
 }
 
 // active regions of an nx x ny x nz grid

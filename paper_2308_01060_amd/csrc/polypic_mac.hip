@@ -184,10 +184,19 @@ __global__ __launch_bounds__(kMacBS) void mac_p2g_kernel(MacP2GArgs a) {
 // measured choice)
 constexpr int kMacG2PBS = 512;
 
-template <int NR>
-__global__ __launch_bounds__(kMacG2PBS) void mac_g2p_kernel(MacG2PArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.P) return;
+// kLines: the rows are staged in LDS and written in whole lines (rows_out_lines).
+template <int NR, int BS, bool kLines>
+__global__ __launch_bounds__(BS) void mac_g2p_kernel(MacG2PArgs a) {
+  constexpr int NW = BS / kWave;
+  constexpr int kRows = NR + 1 > 9 ? NR + 1 : 9;  // a component, or F
+  __shared__ alignas(16) float stage[kLines ? kRows * BS : 1];
+  const int64_t i0 = (int64_t)blockIdx.x * BS;
+  const int tid = threadIdx.x;
+  const int n_slots = (int)min((int64_t)BS, a.P - i0);
+  // (a thread past the slots repeats the last one and writes nothing)
+  const bool in = tid < n_slots;
+  if (!kLines && !in) return;
+  const int64_t i = i0 + min(tid, n_slots - 1);
   const size_t Ps = (size_t)a.P;
   const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
   const size_t N = (size_t)nx * ny * nz;
@@ -198,7 +207,7 @@ __global__ __launch_bounds__(kMacG2PBS) void mac_g2p_kernel(MacG2PArgs a) {
   bool ok = face_axes(xp[0], a.g.ox, a.g.inv_dx, nx, b[0], t[0], bs[0], ts[0]);
   ok &= face_axes(xp[1], a.g.oy, a.g.inv_dx, ny, b[1], t[1], bs[1], ts[1]);
   ok &= face_axes(xp[2], a.g.oz, a.g.inv_dx, nz, b[2], t[2], bs[2], ts[2]);
-  if (!ok) raise_flag(a.status, kFlagRange);
+  if (in && !ok) raise_flag(a.status, kFlagRange);
   float F[9];
   if (a.F_in) {
 #pragma unroll
@@ -228,14 +237,25 @@ __global__ __launch_bounds__(kMacG2PBS) void mac_g2p_kernel(MacG2PArgs a) {
 #pragma unroll
       for (int r = 0; r < 27; ++r) c[r] = 0.0f;
     }
-    float* co = a.coeff_out + (size_t)ax * NR * Ps + i;
+    float xn = fmaf(a.dt, c[0], xp[ax]);
+    xn = fmaxf(xn, a.lo[ax]);
+    xn = fminf(xn, a.hi[ax]);
+    if constexpr (kLines) {
+      float* const row = stage + tid;
+      row[0] = xn;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) __builtin_nontemporal_store(c[r], co + (size_t)r * Ps);
-    if (a.x_out) {
-      float xn = fmaf(a.dt, c[0], xp[ax]);
-      xn = fmaxf(xn, a.lo[ax]);
-      xn = fminf(xn, a.hi[ax]);
-      __builtin_nontemporal_store(xn, a.x_out + (size_t)ax * Ps + i);
+      for (int r = 0; r < NR; ++r) row[(1 + r) * BS] = c[r];
+      __syncthreads();
+      float* const co = a.coeff_out + (size_t)ax * NR * Ps + i0;
+      rows_out_lines<NW, NR>(stage + BS, n_slots, tid, [&](int k) { return co + (size_t)k * Ps; });
+      if (a.x_out)
+        rows_out_lines<NW, 1>(stage, n_slots, tid, [&](int) { return a.x_out + (size_t)ax * Ps + i0; });
+      __syncthreads();  // the next component overwrites the stage
+    } else {
+      float* co = a.coeff_out + (size_t)ax * NR * Ps + i;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) __builtin_nontemporal_store(c[r], co + (size_t)r * Ps);
+      if (a.x_out) __builtin_nontemporal_store(xn, a.x_out + (size_t)ax * Ps + i);
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) lin[ax][q] = (NR >= 4) ? c[1 + q] : 0.0f;
@@ -249,10 +269,19 @@ __global__ __launch_bounds__(kMacG2PBS) void mac_g2p_kernel(MacG2PArgs a) {
         float acc = 0.0f;
 #pragma unroll
         for (int k = 0; k < 3; ++k) acc = fmaf(lin[r][k], F[3 * k + col], acc);
-        __builtin_nontemporal_store(fmaf(s, acc, F[3 * r + col]),
-                                     a.F_out + (size_t)(3 * r + col) * Ps + i);
+        const float f = fmaf(s, acc, F[3 * r + col]);
+        if constexpr (kLines)
+          stage[(3 * r + col) * BS + tid] = f;
+        else
+          __builtin_nontemporal_store(f, a.F_out + (size_t)(3 * r + col) * Ps + i);
       }
+    if constexpr (kLines) {
+      __syncthreads();
+      rows_out_lines<NW, 9>(stage, n_slots, tid,
+                            [&](int k) { return a.F_out + (size_t)k * Ps + i0; });
+    }
   }
+  if (!in) return;
   if (a.mass_out) __builtin_nontemporal_store(a.mass_in[p], a.mass_out + i);
 }
 
@@ -288,8 +317,17 @@ hipError_t mac_p2g_nr(const MacP2GArgs& a, hipStream_t s) {
 
 template <int NR>
 hipError_t mac_g2p_nr(const MacG2PArgs& a, hipStream_t s) {
+  if constexpr (NR == 27) {
+    // (measured, 27 modes: 546 -> 289 us at P = 4000037, 258 at 4000064; 512 threads against
+    // 256: 289 and 309)
+    if (rows_want_lines(NR, 64, a.P, {a.coeff_out, a.x_out})) {
+      constexpr int BS = 512;
+      mac_g2p_kernel<NR, BS, true><<<(unsigned)((a.P + BS - 1) / BS), BS, 0, s>>>(a);
+      return hipGetLastError();
+    }
+  }
   const unsigned blocks = (unsigned)((a.P + kMacG2PBS - 1) / kMacG2PBS);
-  mac_g2p_kernel<NR><<<blocks, kMacG2PBS, 0, s>>>(a);
+  mac_g2p_kernel<NR, kMacG2PBS, false><<<blocks, kMacG2PBS, 0, s>>>(a);
   return hipGetLastError();
 }
 
