@@ -12,12 +12,12 @@
 // P2G: one thread per sorted slot; lane pairs take consecutive slots (which usually
 // share a cell) and the pairs of a wavefront are spread over the workgroup's chunk.
 // Per distinct 4^3 tile of node bases (the cell-key sort makes them contiguous) a
-// workgroup keeps an FP64 LDS brick of 7^3 faces x 6 channels (3 face masses, 3 face
-// momenta), one face below the tile and two above.  A component's 27 face values per
+// workgroup keeps an FP64 LDS brick of 7^3 faces, one face below the tile and two above,
+// for one component's face mass and momentum at a time.  A component's 27 face values per
 // channel are added across a pair whose stencils of that component coincide (one DPP
 // fold each), and one lane of the pair adds them to the brick with LDS atomics, one z
-// plane at a time; the brick is flushed with one float atomic per non-zero face
-// value.  Tiles past the brick budget add straight to HBM.
+// plane at a time; after each component the brick is flushed with one float atomic per
+// non-zero face value.  Tiles past the brick budget add straight to HBM.
 // G2P: one thread per output slot, gathering each component's 27 face velocities
 // and projecting them with that component's rows (section 3.3), then advection and
 // the F update, as on the collocated grid.
@@ -28,14 +28,20 @@ namespace polypic {
 
 namespace {
 
-constexpr int kMacN = 7;                                       // brick edge in faces
-constexpr int kMacNodes = kMacN * kMacN * kMacN;               // 343
-constexpr int kMacSY = 7;                                      // y stride (doubles)
-constexpr int kMacSZ = 49;                                     // z stride (doubles)
-constexpr int kMacV = kMacNodes;                               // 343 doubles per channel:
-                                                               // 36 KB of LDS, 4 groups per CU
-constexpr int kMacCh = 6;                                      // m_x m_y m_z p_x p_y p_z
-constexpr int kMacK = 2;                                       // bricks per workgroup
+constexpr int kMacN = 7;                          // brick edge in faces
+constexpr int kMacNodes = kMacN * kMacN * kMacN;  // 343
+// A round per component, of its face mass and momentum: the bricks of one component are a
+// third of all six channels', so three fit (with two, 0.3 % of a dense block's slots, and
+// 4.5 % of a 16^3-cell block's, went to HBM with 162 atomics each) and may be padded: with
+// strides 8 and 60 (4 short of a multiple of 32) the cells of a half wavefront fall on
+// distinct banks, with dense ones (7 and 49) not.  The kernel is bound by its LDS atomics
+// (measured, 4.0 M particles, 1, 8 and 27 modes: dense, two bricks, 617, 630 and 689 us;
+// dense in rounds 547, 563 and -; now 432, 445 and 570).
+constexpr int kMacSY = 8;   // y stride (doubles)
+constexpr int kMacSZ = 60;  // z stride (doubles)
+constexpr int kMacV = (kMacN - 1) * (1 + kMacSY + kMacSZ) + 1;  // doubles per channel
+constexpr int kMacCh = 2;   // channels of a round
+constexpr int kMacK = 3;    // bricks per workgroup
 constexpr int kMacBS = 256;
 
 // u = (x - o) inv_dx with two float32 roundings; the node stencil (b, t) and the
@@ -55,7 +61,7 @@ __device__ __forceinline__ bool face_axes(float x, float o, float inv_dx, int n,
 }
 
 template <int NR>
-__global__ __launch_bounds__(kMacBS) void mac_p2g_kernel(MacP2GArgs a) {
+__global__ __launch_bounds__(kMacBS, 4) void mac_p2g_kernel(MacP2GArgs a) {
   constexpr int BS = kMacBS;
   constexpr int NW = BS / kWave;
   __shared__ double brick[kMacK * kMacCh * kMacV];
@@ -86,11 +92,22 @@ __global__ __launch_bounds__(kMacBS) void mac_p2g_kernel(MacP2GArgs a) {
     }
   }
   const float m = valid ? (a.mass ? a.mass[p] : a.uniform_mass) : 0.0f;
-  for (int n = tid; n < kMacNodes; n += BS) {
-    const int lz = n / (kMacN * kMacN), ly = (n / kMacN) % kMacN, lx = n % kMacN;
-    const int off = lx + kMacSY * ly + kMacSZ * lz;
+  // this thread's faces of every brick (it clears and flushes them): tid, and tid + BS
+  constexpr int kOwn = (kMacNodes + BS - 1) / BS;
+  auto own_face = [&](int q, int& lx, int& ly, int& lz) {
+    const int n = tid + q * BS;
+    lz = n / (kMacN * kMacN);
+    ly = (n / kMacN) % kMacN;
+    lx = n % kMacN;
+    return n < kMacNodes;
+  };
 #pragma unroll
-    for (int k = 0; k < kMacK * kMacCh; ++k) brick[k * kMacV + off] = 0.0;
+  for (int q = 0; q < kOwn; ++q) {
+    int lx, ly, lz;
+    if (!own_face(q, lx, ly, lz)) break;
+#pragma unroll
+    for (int k = 0; k < kMacK * kMacCh; ++k)
+      brick[k * kMacV + lx + kMacSY * ly + kMacSZ * lz] = 0.0;
   }
   const int seg = plan_bricks<BS, kMacK>(plan, seg_tile, tid, slot,
                                          valid ? brick_tile_id(0, b[0], b[1], b[2]) : kNoTile);
@@ -98,16 +115,11 @@ __global__ __launch_bounds__(kMacBS) void mac_p2g_kernel(MacP2GArgs a) {
   // brick origin: one face below the tile of node bases, on every axis
   const int o0 = (b[0] & ~3) - 1, o1 = (b[1] & ~3) - 1, o2 = (b[2] & ~3) - 1;
 
+  const int nb = plan.n_bricks < kMacK ? plan.n_bricks : kMacK;
   // Every lane runs the component loop (an idle one with zero mass and coefficients),
   // since the pair folds read the partner lane through DPP.
 #pragma unroll 1
   for (int ax = 0; ax < 3; ++ax) {
-    // component ax: node stencil along axis ax, shifted stencil along the others
-    const int c0 = ax == 0 ? b[0] : bs[0], c1 = ax == 1 ? b[1] : bs[1],
-              c2 = ax == 2 ? b[2] : bs[2];
-    const Rows Rx = p2g_rows_scaled(basis_p2g(ax == 0 ? t[0] : ts[0]), m);
-    const Rows Ry = p2g_rows_scaled(basis_p2g(ax == 1 ? t[1] : ts[1]), 1.0f);
-    const Rows Rz = p2g_rows_scaled(basis_p2g(ax == 2 ? t[2] : ts[2]), 1.0f);
     float c[27];
 #pragma unroll
     for (int r = 0; r < 27; ++r) c[r] = 0.0f;
@@ -116,6 +128,12 @@ __global__ __launch_bounds__(kMacBS) void mac_p2g_kernel(MacP2GArgs a) {
 #pragma unroll
       for (int r = 0; r < NR; ++r) c[r] = cp[(size_t)r * Ps];
     }
+    // component ax: node stencil along axis ax, shifted stencil along the others
+    const int c0 = ax == 0 ? b[0] : bs[0], c1 = ax == 1 ? b[1] : bs[1],
+              c2 = ax == 2 ? b[2] : bs[2];
+    const Rows Rx = p2g_rows_scaled(basis_p2g(ax == 0 ? t[0] : ts[0]), m);
+    const Rows Ry = p2g_rows_scaled(basis_p2g(ax == 1 ? t[1] : ts[1]), 1.0f);
+    const Rows Rz = p2g_rows_scaled(basis_p2g(ax == 2 ? t[2] : ts[2]), 1.0f);
     // a pair folds when both lanes' stencils of this component coincide
     const PairFold pf = pair_fold_plan(valid ? ((c2 * 1024 + c1) * 1024 + c0) : -1 - lane, seg,
                                        valid, lane);
@@ -123,8 +141,8 @@ __global__ __launch_bounds__(kMacBS) void mac_p2g_kernel(MacP2GArgs a) {
     const size_t gb = ((size_t)c2 * ny + c1) * nx + c0;
     const size_t sy = (size_t)nx, sz = (size_t)nx * ny;
     auto emitter = [&](int ch) {
-      double* const lbc = brick + ((lds ? seg : 0) * kMacCh + ch) * kMacV + lbase;
-      float* const gc = (ch < 3 ? a.fm : a.fp) + (size_t)(ch % 3) * N + gb;
+      double* const lbc = brick + (lds ? (seg * kMacCh + ch) * kMacV + lbase : 0);
+      float* const gc = (ch == 0 ? a.fm : a.fp) + (size_t)ax * N + gb;
       return [=](int jz, float (&v)[9]) {
         float w[9];
 #pragma unroll
@@ -149,34 +167,32 @@ __global__ __launch_bounds__(kMacBS) void mac_p2g_kernel(MacP2GArgs a) {
       float one[27];
 #pragma unroll
       for (int r = 0; r < 27; ++r) one[r] = r == 0 ? 1.0f : 0.0f;
-      stream_modes_planes<1>(one, Rx, Ry, Rz, emitter(ax));
+      stream_modes_planes<1>(one, Rx, Ry, Rz, emitter(0));
     }
-    stream_modes_planes<NR>(c, Rx, Ry, Rz, emitter(3 + ax));
-  }
-  __syncthreads();
-
-  // flush: thread t owns faces t, t + BS, ... of every brick
-  const int nb = plan.n_bricks < kMacK ? plan.n_bricks : kMacK;
-  for (int n = tid; n < kMacNodes; n += BS) {
-    const int lz = n / (kMacN * kMacN), ly = (n / kMacN) % kMacN, lx = n % kMacN;
-    const int off = lx + kMacSY * ly + kMacSZ * lz;
-    for (int k = 0; k < nb; ++k) {
-      int gx, gy, gz;
-      brick_origin(seg_tile[k], 1, gx, gy, gz);
-      gx += lx;
-      gy += ly;
-      gz += lz;
-      if (gx < 0 || gy < 0 || gz < 0 || gx >= nx || gy >= ny || gz >= nz) continue;
-      const size_t f = ((size_t)gz * ny + gy) * nx + gx;
+    stream_modes_planes<NR>(c, Rx, Ry, Rz, emitter(1));
+    __syncthreads();
+    // flush of the round, by the faces' owners, who clear them for the next component
 #pragma unroll
-      for (int ch = 0; ch < kMacCh; ++ch) {
-        const double v = brick[(k * kMacCh + ch) * kMacV + off];
-        if (v != 0.0) {
-          float* dst = (ch < 3 ? a.fm : a.fp) + (size_t)(ch % 3) * N + f;
-          atomicAdd(dst, (float)v);
-        }
+    for (int q = 0; q < kOwn; ++q) {
+      int lx, ly, lz;
+      if (!own_face(q, lx, ly, lz)) break;
+      for (int k = 0; k < nb; ++k) {
+        int gx, gy, gz;
+        brick_origin(seg_tile[k], 1, gx, gy, gz);
+        gx += lx;
+        gy += ly;
+        gz += lz;
+        if (gx < 0 || gy < 0 || gz < 0 || gx >= nx || gy >= ny || gz >= nz) continue;
+        double* const src = brick + k * kMacCh * kMacV + lx + kMacSY * ly + kMacSZ * lz;
+        const double vm = src[0], vp = src[kMacV];
+        src[0] = 0.0;
+        src[kMacV] = 0.0;
+        const size_t f = (size_t)ax * N + ((size_t)gz * ny + gy) * nx + gx;
+        if (vm != 0.0) atomicAdd(a.fm + f, (float)vm);
+        if (vp != 0.0) atomicAdd(a.fp + f, (float)vp);
       }
     }
+    if (ax < 2) __syncthreads();
   }
 }
 

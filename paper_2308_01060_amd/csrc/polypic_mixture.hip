@@ -8,9 +8,9 @@
 // own grid-summed mass (Eq. 17, 20), and G2P fits each particle from its own phase.
 //
 // P2G: one thread per sorted slot; lane pairs take consecutive slots and the pairs of
-// a wavefront are spread over the workgroup's chunk.  FP64 LDS bricks of 6^3 nodes x 8
-// channels for the first two distinct 4^3 tiles of the chunk -- fluid and solid
-// particles of a tile share its brick -- take the node values, added first across a
+// a wavefront are spread over the workgroup's chunk.  FP64 LDS bricks of 6^3 nodes for
+// the first three distinct 4^3 tiles of the chunk -- fluid and solid particles of a tile
+// share its brick, two channels of either phase at a time -- take the node values, added first across a
 // pair with the same stencil and phase (one DPP fold each), one z plane at a time;
 // one float atomic per non-zero brick value at the flush; other tiles add to HBM.
 // The nodal values are the separable three-stage contraction of the plain P2G.
@@ -21,16 +21,15 @@ namespace polypic {
 
 namespace {
 
-constexpr int kMixK = 2;
-constexpr int kMixCh = 8;  // fluid m, p_x, p_y, p_z, then solid m, p_x, p_y, p_z
 constexpr int kMixBS = 256;
-// dense 6^3 bricks (27 KB of LDS for two bricks of 8 channels: 5 groups per CU)
-constexpr int kMixSY = 6;
-constexpr int kMixSZ = 36;
-constexpr int kMixV = kBrickNodes;
+constexpr int kMixK = 3;   // bricks per workgroup
+constexpr int kMixCh = 4;  // channels of a round: two, of either phase
+constexpr int kMixSY = 8;
+constexpr int kMixSZ = 60;
+constexpr int kMixV = (kBrickN - 1) * (1 + kMixSY + kMixSZ) + 1;
 
 template <int NR>
-__global__ __launch_bounds__(kMixBS) void mixture_p2g_kernel(MixtureP2GArgs a) {
+__global__ __launch_bounds__(kMixBS, 4) void mixture_p2g_kernel(MixtureP2GArgs a) {
   constexpr int BS = kMixBS;
   constexpr int NW = BS / kWave;
   __shared__ double brick[kMixK * kMixCh * kMixV];
@@ -70,11 +69,13 @@ __global__ __launch_bounds__(kMixBS) void mixture_p2g_kernel(MixtureP2GArgs a) {
     t[0] = t[1] = t[2] = 0.0f;
   }
 
-  for (int n = tid; n < kBrickNodes; n += BS) {
-    const BrickNode bn = brick_node(n);
-    const int off = bn.lx + kMixSY * bn.ly + kMixSZ * bn.lz;
+  // the brick node of this thread in every brick (it clears and flushes it)
+  static_assert(kBrickNodes <= BS, "one brick node per thread");
+  const BrickNode bn = brick_node(tid);
+  const int own = bn.lx + kMixSY * bn.ly + kMixSZ * bn.lz;
+  if (tid < kBrickNodes) {
 #pragma unroll
-    for (int k = 0; k < kMixK * kMixCh; ++k) brick[k * kMixV + off] = 0.0;
+    for (int k = 0; k < kMixK * kMixCh; ++k) brick[k * kMixV + own] = 0.0;
   }
   const int seg = plan_bricks<BS, kMixK>(plan, seg_tile, tid, slot,
                                          valid ? brick_tile_id(0, b[0], b[1], b[2]) : kNoTile);
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(kMixBS) void mixture_p2g_kernel(MixtureP2GArgs a) {
     const size_t sy = (size_t)nx, sz = (size_t)nx * ny;
     // channel ch of this particle's phase: 0 mass, 1-3 momentum
     auto emitter = [&](int ch) {
-      double* const lbc = brick + ((lds ? seg : 0) * kMixCh + 4 * ph + ch) * kMixV + lbase;
+      double* const lbc = brick + (lds ? (seg * kMixCh + 2 * ph + (ch & 1)) * kMixV + lbase : 0);
       float* const gc = ch == 0 ? a.gm + (size_t)ph * N + gbase
                                 : a.gp + ((size_t)ph * 3 + (ch - 1)) * N + gbase;
       return [=](int jz, float (&v)[9]) {
@@ -122,6 +123,7 @@ __global__ __launch_bounds__(kMixBS) void mixture_p2g_kernel(MixtureP2GArgs a) {
       for (int r = 0; r < 27; ++r) one[r] = r == 0 ? 1.0f : 0.0f;
       stream_modes_planes<1>(one, Rx, Ry, Rz, emitter(0));
     }
+    const int nb = plan.n_bricks < kMixK ? plan.n_bricks : kMixK;
 #pragma unroll 1
     for (int al = 0; al < 3; ++al) {
       float c[27];
@@ -132,29 +134,29 @@ __global__ __launch_bounds__(kMixBS) void mixture_p2g_kernel(MixtureP2GArgs a) {
         for (int r = 0; r < NR; ++r) c[r] = a.coeff[((size_t)al * NR + r) * Ps + p];
       }
       stream_modes_planes<NR>(c, Rx, Ry, Rz, emitter(1 + al));
-    }
-  }
-  __syncthreads();
-
-  const int nb = plan.n_bricks < kMixK ? plan.n_bricks : kMixK;
-  for (int n = tid; n < kBrickNodes; n += BS) {
-    const BrickNode bn = brick_node(n);
-    const int off = bn.lx + kMixSY * bn.ly + kMixSZ * bn.lz;
-    for (int k = 0; k < nb; ++k) {
-      int o0, o1, o2;
-      brick_origin(seg_tile[k], 0, o0, o1, o2);
-      const int gx = o0 + bn.lx, gy = o1 + bn.ly, gz = o2 + bn.lz;
-      if (gx >= nx || gy >= ny || gz >= nz) continue;
-      const size_t f = ((size_t)gz * ny + gy) * nx + gx;
+      if (al == 1) continue;  // (uniform) a round ends with p_x, and with p_z
+      __syncthreads();
+      // flush of the round: channels 0 and 1, then 2 and 3, of either phase; the nodes'
+      // owners clear them for the next round
+      for (int k = 0; tid < kBrickNodes && k < nb; ++k) {
+        int o0, o1, o2;
+        brick_origin(seg_tile[k], 0, o0, o1, o2);
+        const int gx = o0 + bn.lx, gy = o1 + bn.ly, gz = o2 + bn.lz;
+        if (gx >= nx || gy >= ny || gz >= nz) continue;
+        const size_t f = ((size_t)gz * ny + gy) * nx + gx;
 #pragma unroll
-      for (int ch = 0; ch < kMixCh; ++ch) {
-        const double v = brick[(k * kMixCh + ch) * kMixV + off];
-        if (v == 0.0) continue;
-        const int k4 = ch & 3, phase = ch >> 2;
-        float* dst = k4 == 0 ? a.gm + (size_t)phase * N + f
-                             : a.gp + ((size_t)phase * 3 + (k4 - 1)) * N + f;
-        atomicAdd(dst, (float)v);
+        for (int q = 0; q < kMixCh; ++q) {
+          double* const src = brick + (k * kMixCh + q) * kMixV + own;
+          const double v = *src;
+          *src = 0.0;
+          if (v == 0.0) continue;
+          const int phase = q >> 1, k4 = (al == 0 ? 0 : 2) + (q & 1);
+          float* dst = k4 == 0 ? a.gm + (size_t)phase * N + f
+                               : a.gp + ((size_t)phase * 3 + (k4 - 1)) * N + f;
+          atomicAdd(dst, (float)v);
+        }
       }
+      if (al == 0) __syncthreads();
     }
   }
 }
