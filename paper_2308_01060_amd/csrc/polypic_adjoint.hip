@@ -210,8 +210,7 @@ __global__ __launch_bounds__(256) void p2g_backward_kernel(P2GBackArgs a) {
     xg[2] = fmaf(m, sz, xg[2]);
     if constexpr (kLines) {
       __syncthreads();
-      float* const rows = a.coeff_grad + (size_t)ax * NR * Ps + i0;
-      rows_out_lines<NW, NR>(stage, n_slots, tid, [&](int k) { return rows + (size_t)k * Ps; });
+      rows_out_lines<NW, NR>(stage, a.coeff_grad + (size_t)ax * NR * Ps + i0, Ps, n_slots, tid);
       __syncthreads();  // the next component overwrites the stage
     }
   }

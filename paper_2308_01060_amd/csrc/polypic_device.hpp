@@ -795,32 +795,36 @@ __device__ __forceinline__ void row_store_body(const float* staged, float* row, 
   __builtin_nontemporal_store(Float4{s[0], s[1], s[2], s[3]},
                               reinterpret_cast<Float4*>(row + at));
 }
+template <bool kStream = false>
 __device__ __forceinline__ void row_store_ends(const float* staged, float* row, int n, int body,
                                                int lane) {
   const int at = min(lane + (lane < row_head(row) ? 0 : body), n);  // (n: dropped)
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(staged[min(at, n - 1)]), row_rsrc(row, n),
-                                        at * (int)sizeof(float), 0, 0);
+                                        at * (int)sizeof(float), 0, kStream ? 2 : 0);
 }
-// ROWS rows of a workgroup of NW wavefronts, row k from staged + k * NW * kWave to dst(k); a
-// wavefront takes 4 * kWave slots of a row at a time.  (Bodies first: they are free of
-// branches among themselves.)
-template <int NW, int ROWS, class Dst>
-__device__ __forceinline__ void rows_out_lines(const float* staged, int n, int tid, Dst&& dst) {
+// ROWS rows of a workgroup of NW wavefronts, row k from staged + k * NW * kWave to
+// row0 + k * stride; a wavefront takes 4 * kWave slots of a row at a time, wavefront `w0` the
+// first.  (Bodies first: they are free of branches among themselves.  The row pointers
+// step: a product per row costs more scalar instructions than the rest of the row.)
+template <int NW, int ROWS>
+__device__ __forceinline__ void rows_out_lines(const float* staged, float* row0, size_t stride,
+                                               int n, int tid, int w0 = 0) {
   static_assert(NW % 4 == 0, "whole segments of 4 * kWave slots");
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int body = rows_body(n);  // (uniform)
   auto each = [&](int first, auto step, auto&& put) {
+    const float* s = staged + first * NW * kWave;
+    float* row = row0 + first * stride;
 #pragma unroll
-    for (int k = 0; k < ROWS; k += step)
-      if (k + step <= ROWS || k + first < ROWS)
-        put(staged + (k + first) * NW * kWave, dst(k + first));
+    for (int k = 0; k < ROWS; k += step, s += step * NW * kWave, row += step * stride)
+      if (k + step <= ROWS || k + first < ROWS) put(s, row);
   };
-  const int quad = lane + wave / 4 * kWave;  // this lane's four slots
+  const int quad = NW == 4 ? lane : lane + wave / 4 * kWave;  // this lane's four slots
   if (4 * quad < body)
-    each(wave % 4, std::integral_constant<int, 4>{},
+    each((wave + 4 - w0) % 4, std::integral_constant<int, 4>{},
          [&](const float* s, float* row) { row_store_body(s, row, quad); });
-  each(wave, std::integral_constant<int, NW>{},
+  each((wave + NW - w0) % NW, std::integral_constant<int, NW>{},
        [&](const float* s, float* row) { row_store_ends(s, row, n, body, lane); });
 }
 

@@ -88,7 +88,11 @@ constexpr int kQuadCell = 10;  // particles per cell of a chunk from which quads
 // cells of each chunk and takes quads from kQuadCell particles per cell on (measured, pairs
 // and quads, 27 modes: 194 and 207 us at 8 per cell, 330 and 323 at 12, 457 and 419 at 16;
 // 4 modes: 238 and 203 at 12, 330 and 251 at 16).
-template <int NR, int BS, class Scenes, bool kLines>
+// kRowMode: how the output rows are written.
+constexpr int kBySlot = 0;       // every thread its slot of each row
+constexpr int kLinesCached = 1;  // in whole lines, the rows' ends through the caches
+constexpr int kLinesStream = 2;  // in whole lines, the ends streamed as well
+template <int NR, int BS, class Scenes, int kRowMode>
 __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   constexpr int NW = BS / kWave;
   constexpr int K = kFuseK;
@@ -239,15 +243,24 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   // rows lie past the bricks.
   auto row_at = [&](int k) { return stage + k * BS; };
   // `rows` staged rows out, row k from row_at(k0 + k) to dst(k): every thread its slot, or
-  // in whole lines
+  // in whole lines, a quarter of the rows per wavefront
+  const int wave = __builtin_amdgcn_readfirstlane(wv);
   auto write_rows = [&](auto rows, int k0, auto dst) {
-    if constexpr (kLines) {
-      static_assert(BS == 4 * kWave, "rows of 4 slots per lane");
-      rows_out_lines<NW, rows>(row_at(k0), n_slots, tid, dst);
-    } else {
+    if constexpr (kRowMode == kBySlot) {
 #pragma unroll
       for (int k = 0; k < rows; ++k)
         row_store_nt(row_at(k0 + k)[tid], dst(k), n_slots, tid * (int)sizeof(float));
+    } else {
+      const int body = rows_body(n_slots);  // (uniform)
+      auto each = [&](auto&& put) {
+#pragma unroll
+        for (int k = 0; k < rows; k += NW)
+          if (k + NW <= rows || k + wave < rows) put(row_at(k0 + k + wave), dst(k + wave));
+      };
+      if (4 * lane < body) each([&](const float* s, float* row) { row_store_body(s, row, lane); });
+      each([&](const float* s, float* row) {
+        row_store_ends<kRowMode == kLinesStream>(s, row, n_slots, body, lane);
+      });
     }
   };
   {
@@ -487,17 +500,23 @@ hipError_t launch_nr(const G2P2GArgs& a, const Scenes& sc, unsigned blocks, hipS
   constexpr int BS = kSceneChunk;
   // Whole lines cost more instructions per row than a slot per thread, and pay at 27 modes
   // when the rows start off the 32-byte sectors (measured, a slot per thread and whole
-  // lines: P = 2500007 309 and 251 us, 4194303 493 and 488; P = 2500008 260 and 265,
-  // 4000040 406 and 450; at 4 modes, P = 2500007, 153 and 168).  A batch's workgroups
-  // neighbour each other on one XCD, whose L2 joins the parts of a line: 718 us a slot per
-  // thread, 745 in lines.
-  if constexpr (NR > 8 && std::is_same_v<Scenes, OneScene>) {
+  // lines: P = 1234567 173 and 131 us, 2500007 305 and 240, 4000037 484 and 409; P = 2500008
+  // 260 and 265, 4000040 406 and 450; at 4 modes, P = 2500007, 153 and 168).  The rows' ends
+  // go through the caches while those still hold a line when the neighbouring workgroup's
+  // part of it comes: up to about 4.2 M particles (through the caches and streamed:
+  // 3400007 358 and 380 us, 4000037 409 and 422, 4194303 478 and 458, 5500001 629 and 581).
+  // A batch's workgroups neighbour each other on one XCD, whose L2 joins the parts of a
+  // line: 718 us a slot per thread, 745 in lines.
+  if constexpr (NR == 27 && std::is_same_v<Scenes, OneScene>) {
     if (rows_want_lines(NR, 32, a.P, {a.coeff_out, a.x_out})) {
-      g2p2g_kernel<NR, BS, Scenes, true><<<blocks, BS, 0, stream>>>(a, sc);
+      if (a.P < (int64_t)1 << 22)
+        g2p2g_kernel<NR, BS, Scenes, kLinesCached><<<blocks, BS, 0, stream>>>(a, sc);
+      else
+        g2p2g_kernel<NR, BS, Scenes, kLinesStream><<<blocks, BS, 0, stream>>>(a, sc);
       return hipGetLastError();
     }
   }
-  g2p2g_kernel<NR, BS, Scenes, false><<<blocks, BS, 0, stream>>>(a, sc);
+  g2p2g_kernel<NR, BS, Scenes, kBySlot><<<blocks, BS, 0, stream>>>(a, sc);
   return hipGetLastError();
 }
 

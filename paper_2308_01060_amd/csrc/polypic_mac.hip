@@ -262,10 +262,9 @@ __global__ __launch_bounds__(BS) void mac_g2p_kernel(MacG2PArgs a) {
 #pragma unroll
       for (int r = 0; r < NR; ++r) row[(1 + r) * BS] = c[r];
       __syncthreads();
-      float* const co = a.coeff_out + (size_t)ax * NR * Ps + i0;
-      rows_out_lines<NW, NR>(stage + BS, n_slots, tid, [&](int k) { return co + (size_t)k * Ps; });
+      rows_out_lines<NW, NR>(stage + BS, a.coeff_out + (size_t)ax * NR * Ps + i0, Ps, n_slots, tid);
       if (a.x_out)
-        rows_out_lines<NW, 1>(stage, n_slots, tid, [&](int) { return a.x_out + (size_t)ax * Ps + i0; });
+        rows_out_lines<NW, 1>(stage, a.x_out + (size_t)ax * Ps + i0, Ps, n_slots, tid, 3);
       __syncthreads();  // the next component overwrites the stage
     } else {
       float* co = a.coeff_out + (size_t)ax * NR * Ps + i;
@@ -293,8 +292,7 @@ __global__ __launch_bounds__(BS) void mac_g2p_kernel(MacG2PArgs a) {
       }
     if constexpr (kLines) {
       __syncthreads();
-      rows_out_lines<NW, 9>(stage, n_slots, tid,
-                            [&](int k) { return a.F_out + (size_t)k * Ps + i0; });
+      rows_out_lines<NW, 9>(stage, a.F_out + i0, Ps, n_slots, tid);
     }
   }
   if (!in) return;
