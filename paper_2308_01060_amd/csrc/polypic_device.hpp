@@ -91,10 +91,12 @@ __device__ __forceinline__ bool stencil_axis(float x, float o, float inv_dx, int
   return ok;
 }
 
-// The same with the product kept from contraction into either subtraction, which the
-// rounding intrinsics alone do not keep the compiler from: for a kernel that computes the
-// offsets of one particle in several places, which must agree to the bit.  (The cell keys
-// keep the form above: their roundings decide ties at cell boundaries.)
+// The rounding intrinsics do not keep the compiler from contracting the product into either
+// subtraction, so the last bit of t (and ties of b) is the compiler's choice above.  Two
+// forms that are not, for kernels that need the offsets to the bit: the product apart, for
+// offsets computed in several places of a kernel; and the product contracted into both,
+// which is what the scatters do.  (Nodes that only a stencil's edge reaches have masses
+// down to the square of that last bit.)
 __device__ __forceinline__ bool stencil_axis_apart(float x, float o, float inv_dx, int n, int& b,
                                                    float& t) {
 #pragma clang fp contract(off)
@@ -104,6 +106,15 @@ __device__ __forceinline__ bool stencil_axis_apart(float x, float o, float inv_d
   const bool ok = (f >= 0.0f) && (f <= (float)(n - 3));
   b = ok ? (int)f : 0;
   t = ok ? u - (f + 1.0f) : 0.0f;
+  return ok;
+}
+__device__ __forceinline__ bool stencil_axis_joint(float x, float o, float inv_dx, int n, int& b,
+                                                   float& t) {
+  const float d = x - o;
+  const float f = floorf(fmaf(d, inv_dx, -0.5f));
+  const bool ok = (f >= 0.0f) && (f <= (float)(n - 3));
+  b = ok ? (int)f : 0;
+  t = ok ? fmaf(d, inv_dx, -(f + 1.0f)) : 0.0f;
   return ok;
 }
 

@@ -339,9 +339,9 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   int c0 = 0, c1 = 0, c2 = 0;
   float u0 = 0.f, u1 = 0.f, u2 = 0.f;
   if (valid) {
-    bool ok2 = stencil_axis(xn[0], g.ox, g.inv_dx, nx, c0, u0);
-    ok2 &= stencil_axis(xn[1], g.oy, g.inv_dx, ny, c1, u1);
-    ok2 &= stencil_axis(xn[2], g.oz, g.inv_dx, nz, c2, u2);
+    bool ok2 = stencil_axis_joint(xn[0], g.ox, g.inv_dx, nx, c0, u0);
+    ok2 &= stencil_axis_joint(xn[1], g.oy, g.inv_dx, ny, c1, u1);
+    ok2 &= stencil_axis_joint(xn[2], g.oz, g.inv_dx, nz, c2, u2);
     if (!ok2) {  // (x' is clamped into the grid: only for a grid too small for a stencil)
       raise_flag(a.status, kFlagRange);
       valid = false;

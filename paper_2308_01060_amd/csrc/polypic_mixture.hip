@@ -53,9 +53,9 @@ __global__ __launch_bounds__(kMixBS, 4) void mixture_p2g_kernel(MixtureP2GArgs a
   int ph = 0;
   float m = 0.0f;
   if (in) {
-    bool ok = stencil_axis(a.x[p], a.g.ox, a.g.inv_dx, nx, b[0], t[0]);
-    ok &= stencil_axis(a.x[Ps + p], a.g.oy, a.g.inv_dx, ny, b[1], t[1]);
-    ok &= stencil_axis(a.x[2 * Ps + p], a.g.oz, a.g.inv_dx, nz, b[2], t[2]);
+    bool ok = stencil_axis_joint(a.x[p], a.g.ox, a.g.inv_dx, nx, b[0], t[0]);
+    ok &= stencil_axis_joint(a.x[Ps + p], a.g.oy, a.g.inv_dx, ny, b[1], t[1]);
+    ok &= stencil_axis_joint(a.x[2 * Ps + p], a.g.oz, a.g.inv_dx, nz, b[2], t[2]);
     if (!ok) raise_flag(a.status, kFlagRange);
     ph = a.phase[p];
     const bool ph_ok = ph == 0 || ph == 1;

@@ -205,6 +205,11 @@ int sort_key_bits(const GridDev& g) {
 
 namespace {
 
+template <class Scenes>
+bool small_sort(const Scenes& sc, int mbits, int key_bits, int64_t P, const float* x,
+                const uint32_t* keys_prev, uint32_t* keys_out, int32_t* perm_out, int32_t* status,
+                hipStream_t stream);
+
 // Stable LSD radix sort of the keys the key kernel wrote to (ksrc, vsrc); the
 // last pass lands in (keys_out, perm_out).
 template <class Scenes>
@@ -212,6 +217,8 @@ hipError_t sort_with(const Scenes& sc, int mbits, int key_bits, int64_t P, const
                      uint32_t* keys_out, int32_t* perm_out, void* ws, int32_t* status,
                      hipStream_t stream) {
   if (P == 0) return hipSuccess;
+  if (small_sort(sc, mbits, key_bits, P, x, nullptr, keys_out, perm_out, status, stream))
+    return hipGetLastError();
   const int n_tiles = (int)((P + kSortTile - 1) / kSortTile);
   char* w = (char*)ws;
   uint32_t* keys_alt = (uint32_t*)w;
@@ -481,17 +488,155 @@ constexpr int kWindowCap = 2048;  // changed pairs a workgroup stages in LDS
 // of its base node (of the clamped base node when !ok), with the scene index
 // above bit mbits in a batch.  s: a scene at or before slot i's (advanced here).
 template <class Scenes>
-__device__ __forceinline__ uint32_t cell_key(const Scenes& sc, int mbits,
-                                             const float* __restrict__ x, size_t Ps, int64_t i,
-                                             int& s, bool& ok) {
+__device__ __forceinline__ uint32_t cell_key_at(const Scenes& sc, int mbits, float x0, float x1,
+                                                float x2, int64_t i, int& s, bool& ok) {
   s = sc.of(i, s);
   const SceneGrid g = sc.grid(s);
   int b0, b1, b2;
   float t0, t1, t2;
-  ok = stencil_axis(x[i], g.ox, g.inv_dx, g.nx, b0, t0);
-  ok &= stencil_axis(x[Ps + i], g.oy, g.inv_dx, g.ny, b1, t1);
-  ok &= stencil_axis(x[2 * Ps + i], g.oz, g.inv_dx, g.nz, b2, t2);
+  ok = stencil_axis(x0, g.ox, g.inv_dx, g.nx, b0, t0);
+  ok &= stencil_axis(x1, g.oy, g.inv_dx, g.ny, b1, t1);
+  ok &= stencil_axis(x2, g.oz, g.inv_dx, g.nz, b2, t2);
   return ((uint32_t)s << mbits) | morton3(b0, b1, b2);
+}
+template <class Scenes>
+__device__ __forceinline__ uint32_t cell_key(const Scenes& sc, int mbits,
+                                             const float* __restrict__ x, size_t Ps, int64_t i,
+                                             int& s, bool& ok) {
+  return cell_key_at(sc, mbits, x[i], x[Ps + i], x[2 * Ps + i], i, s, ok);
+}
+
+// The whole sort of a small set in one workgroup and one launch, for the full sort and the
+// re-sort alike (either gives the stable order of the new keys): wave w takes the
+// w'th share of the keys in rounds of 64, ranks them by ballot matching of equal digits
+// as the counted scatter does, and the keys change places in LDS between the passes.  A
+// set this size is bound by its launches: a full sort takes 7 to 13 of them, a re-sort 5 to
+// 7 (measured, 4,096 and 8,192 particles: FILLME).
+constexpr int kSmallBS = 1024;
+constexpr int kSmallWaves = kSmallBS / kWave;
+constexpr int kSmallMax = kSmallBS * kSortIPT;  // particles
+static_assert(kSmallMax <= 65536, "slots and counts fit 16 bits");
+
+template <class Scenes>
+__global__ __launch_bounds__(kSmallBS) void small_sort_kernel(
+    Scenes sc, int mbits, int passes, int P, const float* __restrict__ x,
+    const uint32_t* __restrict__ keys_prev, uint32_t* __restrict__ keys_out,
+    int32_t* __restrict__ perm_out, int32_t* __restrict__ status) {
+  __shared__ uint32_t skey[kSmallMax];
+  __shared__ uint16_t sval[kSmallMax];
+  __shared__ uint16_t whist[kSmallWaves][kRadix];  // per wave: running digit counts
+  __shared__ uint32_t digit_base[kRadix];
+  __shared__ uint32_t wsum[kRadix / kWave];
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wv = tid / kWave;
+  // rounds of 64 keys per wave, as few as the set needs (uniform)
+  const int rounds = (P + kSmallBS - 1) / kSmallBS;
+  const int base = wv * rounds * kWave + lane;
+  uint32_t key[kSortIPT];
+  uint32_t val[kSortIPT], rank[kSortIPT];
+  {
+    // every load first (a slot past P repeats the last): one round trip for all
+    float xs[kSortIPT][3];
+    uint32_t prev[kSortIPT], before[kSortIPT];
+#pragma unroll
+    for (int j = 0; j < kSortIPT; ++j) {
+      if (j >= rounds) break;
+      const int i = min(base + j * kWave, P - 1);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) xs[j][c] = x[(size_t)c * P + i];
+      prev[j] = keys_prev ? keys_prev[i] : 0u;
+      before[j] = keys_prev && i > 0 ? keys_prev[i - 1] : 0u;
+    }
+    int s = sc.first(min(base, P - 1));
+    bool in_range = true, in_order = true;
+#pragma unroll
+    for (int j = 0; j < kSortIPT; ++j) {
+      if (j >= rounds) break;
+      const int i = min(base + j * kWave, P - 1);
+      bool ok;
+      key[j] = cell_key_at(sc, mbits, xs[j][0], xs[j][1], xs[j][2], i, s, ok);
+      val[j] = (uint32_t)i;
+      in_range &= ok;
+      in_order &= before[j] <= prev[j];
+    }
+    if (!in_range) raise_flag(status, kFlagRange);
+    if (!in_order) raise_flag(status, kFlagOrder);
+  }
+  for (int q = 0; q < passes; ++q) {
+    const int shift = 8 * q;
+    for (int k = tid; k < kSmallWaves * kRadix / 2; k += kSmallBS)
+      reinterpret_cast<uint32_t*>(&whist[0][0])[k] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSortIPT; ++j) {
+      if (j >= rounds) break;
+      const bool valid = base + j * kWave < P;
+      const uint32_t d = (key[j] >> shift) & (kRadix - 1);
+      const unsigned long long same = match_digit(d, valid);
+      const int r = lanes_below(same);
+      const uint32_t before = whist[wv][d];  // this wave's keys with digit d so far
+      if (valid && r == 0) whist[wv][d] = (uint16_t)(before + (uint32_t)__popcll(same));
+      rank[j] = before + (uint32_t)r;
+    }
+    __syncthreads();
+    // digit tid: prefix over the waves, then over the digits
+    uint32_t cnt = 0, inc = 0;
+    if (tid < kRadix) {
+      uint32_t c[kSmallWaves];
+#pragma unroll
+      for (int w = 0; w < kSmallWaves; ++w) c[w] = whist[w][tid];
+#pragma unroll
+      for (int w = 0; w < kSmallWaves; ++w) {
+        whist[w][tid] = (uint16_t)cnt;
+        cnt += c[w];
+      }
+      inc = cnt;
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t o = __shfl_up(inc, off, kWave);
+        if (lane >= off) inc += o;
+      }
+      if (lane == kWave - 1) wsum[wv] = inc;
+    }
+    __syncthreads();
+    if (tid < kRadix) {
+      uint32_t pre = 0;
+#pragma unroll
+      for (int w = 0; w < kRadix / kWave; ++w) pre += (w < wv) ? wsum[w] : 0u;
+      digit_base[tid] = pre + inc - cnt;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSortIPT; ++j) {
+      if (j >= rounds) break;
+      if (base + j * kWave < P) {
+        const uint32_t d = (key[j] >> shift) & (kRadix - 1);
+        const uint32_t pos = digit_base[d] + whist[wv][d] + rank[j];  // (a bijection of [0, P))
+        skey[pos] = key[j];
+        sval[pos] = (uint16_t)val[j];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSortIPT; ++j) {
+      if (j >= rounds) break;
+      const int i = base + j * kWave;
+      if (i < P) {
+        key[j] = skey[i];
+        val[j] = sval[i];
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kSortIPT; ++j) {
+    if (j >= rounds) break;
+    const int i = base + j * kWave;
+    if (i < P) {
+      keys_out[i] = key[j];
+      perm_out[i] = (int32_t)val[j];
+    }
+  }
 }
 
 // changed-slot masks, per-workgroup counts, and the order check of keys_prev;
@@ -895,6 +1040,16 @@ __global__ __launch_bounds__(kSortBS) void upd_place_kernel(
                     keys_out, perm_out, window, wk, wi);
 }
 
+template <class Scenes>
+bool small_sort(const Scenes& sc, int mbits, int key_bits, int64_t P, const float* x,
+                const uint32_t* keys_prev, uint32_t* keys_out, int32_t* perm_out, int32_t* status,
+                hipStream_t stream) {
+  if (P > kSmallMax) return false;
+  small_sort_kernel<Scenes><<<1, kSmallBS, 0, stream>>>(sc, mbits, (key_bits + 7) / 8, (int)P, x,
+                                                        keys_prev, keys_out, perm_out, status);
+  return true;
+}
+
 struct UpdLayout {
   unsigned long long* mask;
   uint32_t *blk, *gpre, *count, *ck0, *ck1, *look, *totals, *tile_ctr;
@@ -943,6 +1098,8 @@ hipError_t sort_update_with(const Scenes& sc, int mbits, int key_bits, int64_t P
   const int n_tiles = (int)((P + kSortTile - 1) / kSortTile);
   const int passes = (key_bits + 7) / 8;
   if (passes < 1 || passes > kMaxPasses) return hipErrorInvalidValue;
+  if (small_sort(sc, mbits, key_bits, P, x, keys_prev, keys_out, perm_out, status, stream))
+    return hipGetLastError();
   upd_mask_kernel<Scenes><<<n_tiles, kSortBS, 0, stream>>>(sc, mbits, P, x, keys_prev, L.mask,
                                                            L.blk, L.totals, L.tile_ctr, status);
   const bool scanned = n_tiles > kFoldedScanMaxTiles;
