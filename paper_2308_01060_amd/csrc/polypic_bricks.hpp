@@ -8,41 +8,65 @@
 // of a chunk in arbitrary order beyond its first K tiles) add to HBM instead.
 #pragma once
 
+#include <type_traits>
+
 #include "polypic_device.hpp"
 
 namespace polypic {
 
+struct NoCells {};
 template <int BS>
-struct BrickPlan {
+struct CellsOf {
+  uint32_t cell_of[BS];  // cell of slot t
+};
+template <int BS, bool kCells = false>
+struct BrickPlan : std::conditional_t<kCells, CellsOf<BS>, NoCells> {
   uint64_t tile_of[BS];     // tile of slot t
-  int run_of[BS];           // run index of slot t (-1 before the first valid slot)
+  std::conditional_t<kCells, int16_t, int> run_of[BS];  // run index of slot t (-1 before the first valid slot)
   uint64_t run_tile[kWave]; // tiles of the first kWave runs
   int run_brick[kWave];     // distinct-tile index of each of those runs
-  int wave_heads[BS / kWave];
+  int wave_heads[BS / kWave];  // heads of runs, and of cells << 16
   int n_bricks;             // distinct tiles among the first kWave runs
 };
+
+// brick of a planned slot: see plan_bricks
+template <int BS, int K, bool kCells>
+__device__ __forceinline__ int brick_of_slot(const BrickPlan<BS, kCells>& plan, int slot) {
+  const int run = plan.run_of[slot];
+  // a run past the first kWave keeps a value of its own (never below K)
+  return run < 0 ? -1 : (run < kWave ? plan.run_brick[run] : K + run);
+}
 
 // Called by every thread of the workgroup (it holds barriers), with the tile of the
 // slot the thread processes (kNoTile if none).  Returns that slot's brick: in [0, K)
 // for an LDS brick, >= K for HBM, -1 for no tile.  seg_tile[d] receives the tile of
 // brick d < K; plan.n_bricks the number of distinct tiles seen.
-template <int BS, int K>
-__device__ __forceinline__ int plan_bricks(BrickPlan<BS>& plan, uint64_t* seg_tile, int tid,
-                                           int slot, uint64_t tile) {
+// With kCells the slots' cells are given as well (a number each, different for different
+// cells) and counted (plan_cells).
+template <int BS, int K, bool kCells = false>
+__device__ __forceinline__ int plan_bricks(BrickPlan<BS, kCells>& plan, uint64_t* seg_tile, int tid,
+                                           int slot, uint64_t tile, uint32_t cell = 0) {
   constexpr int NW = BS / kWave;
+  constexpr int kRunMask = kCells ? 0xFFFF : ~0;
   const int lane = tid & (kWave - 1);
   const int wv = tid / kWave;
   plan.tile_of[slot] = tile;
+  if constexpr (kCells) plan.cell_of[slot] = cell;
   __syncthreads();
   {
     const uint64_t tt = plan.tile_of[tid];
     const bool head = tt != kNoTile && (tid == 0 || plan.tile_of[tid - 1] != tt);
     const unsigned long long hb = __ballot(head);
-    if (lane == 0) plan.wave_heads[wv] = __popcll(hb);
+    int cells = 0;
+    if constexpr (kCells) {
+      const bool first = tt != kNoTile && (head || plan.cell_of[tid - 1] != plan.cell_of[tid]);
+      cells = __popcll(__ballot(first));
+    }
+    if (lane == 0) plan.wave_heads[wv] = __popcll(hb) | (kCells ? cells << 16 : 0);
     __syncthreads();
     int pre = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) pre += (w < wv) ? plan.wave_heads[w] : 0;
+    for (int w = 0; w < NW; ++w) pre += (w < wv) ? plan.wave_heads[w] & kRunMask : 0;
     const int run = pre + lanes_below(hb) + (head ? 1 : 0) - 1;
     plan.run_of[tid] = run;
     if (head && run < kWave) plan.run_tile[run] = tt;
@@ -51,7 +75,7 @@ __device__ __forceinline__ int plan_bricks(BrickPlan<BS>& plan, uint64_t* seg_ti
   if (wv == 0) {
     int nruns = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) nruns += plan.wave_heads[w];
+    for (int w = 0; w < NW; ++w) nruns += plan.wave_heads[w] & kRunMask;
     const int nr = nruns < kWave ? nruns : kWave;
     const uint64_t mine = lane < nr ? plan.run_tile[lane] : kNoTile;
     int first_same = lane;  // first run with this run's tile
@@ -66,9 +90,16 @@ __device__ __forceinline__ int plan_bricks(BrickPlan<BS>& plan, uint64_t* seg_ti
     if (lane == 0) plan.n_bricks = __popcll(fb);
   }
   __syncthreads();
-  const int run = plan.run_of[slot];
-  // a run past the first kWave keeps a value of its own (never below K)
-  return run < 0 ? -1 : (run < kWave ? plan.run_brick[run] : K + run);
+  return brick_of_slot<BS, K, kCells>(plan, slot);
+}
+
+// cells counted by plan_bricks (uniform over the workgroup)
+template <int BS>
+__device__ __forceinline__ int plan_cells(const BrickPlan<BS, true>& plan) {
+  int cells = 0;
+#pragma unroll
+  for (int w = 0; w < BS / kWave; ++w) cells += plan.wave_heads[w] >> 16;
+  return __builtin_amdgcn_readfirstlane(cells);
 }
 
 // Slot of a thread for lane-pair scatters: pairs of consecutive sorted slots (which in
@@ -79,6 +110,14 @@ __device__ __forceinline__ int pair_slot(int tid) {
   const int lane = tid & (kWave - 1);
   const int wv = tid / kWave;
   return ((((lane >> 1) * NW + wv)) << 1) | (lane & 1);
+}
+
+// The same for quads: four consecutive slots, the quads NW quads apart.
+template <int NW>
+__device__ __forceinline__ int quad_slot(int tid) {
+  const int lane = tid & (kWave - 1);
+  const int wv = tid / kWave;
+  return ((((lane >> 2) * NW + wv)) << 2) | (lane & 3);
 }
 
 // Lane-pair fold of a scatter: `key` identifies what a lane scatters to (its stencil
@@ -96,6 +135,18 @@ __device__ __forceinline__ PairFold pair_fold_plan(int key, int seg, bool scatte
   pf.f = pair ? 1.0f : 0.0f;
   pf.emit = scatters && (!pair || (lane & 1) == 0);
   return pf;
+}
+
+// A quad whose pairs both fold and agree folds once more, if asked (uniform): its first
+// lane emits.  Returns the factor of the second fold.
+__device__ __forceinline__ float quad_fold_plan(bool quads, int key, int seg, bool scatters,
+                                                int lane, PairFold& pf) {
+  if (!quads) return 0.0f;
+  const int pair = pf.f != 0.0f;
+  const bool quad = pair && quad_swap_i(pair) != 0 && key == quad_swap_i(key) &&
+                    seg == quad_swap_i(seg);
+  if (quad) pf.emit = scatters && (lane & 3) == 0;
+  return quad ? 1.0f : 0.0f;
 }
 
 // Origin (first node) of the brick of tile `tl` along each axis, for bricks that start

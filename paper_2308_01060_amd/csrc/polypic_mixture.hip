@@ -22,6 +22,7 @@ namespace polypic {
 namespace {
 
 constexpr int kMixBS = 256;
+constexpr int kMixQuadCell = 10;  // particles per cell of a chunk from which quads fold
 constexpr int kMixK = 3;   // bricks per workgroup
 constexpr int kMixCh = 4;  // channels of a round: two, of either phase
 constexpr int kMixSY = 8;
@@ -33,41 +34,45 @@ __global__ __launch_bounds__(kMixBS, 4) void mixture_p2g_kernel(MixtureP2GArgs a
   constexpr int BS = kMixBS;
   constexpr int NW = BS / kWave;
   __shared__ double brick[kMixK * kMixCh * kMixV];
-  __shared__ BrickPlan<BS> plan;
+  __shared__ BrickPlan<BS, true> plan;
   __shared__ uint64_t seg_tile[kMixK];
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
-  const int slot = pair_slot<NW>(tid);
-  const int64_t i = (int64_t)blockIdx.x * BS + slot;
-  const bool in = i < a.P;
   const size_t Ps = (size_t)a.P;
   const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
   const size_t N = (size_t)nx * ny * nz;
-  int p = 0;
-  if (in) p = a.perm ? min(max(a.perm[i], 0), (int)(a.P - 1)) : (int)i;
-
+  int p = 0, ph = 0;
   int b[3] = {0, 0, 0};
   float t[3] = {0.f, 0.f, 0.f};
-  bool valid = in;
-  int ph = 0;
   float m = 0.0f;
-  if (in) {
-    bool ok = stencil_axis_joint(a.x[p], a.g.ox, a.g.inv_dx, nx, b[0], t[0]);
-    ok &= stencil_axis_joint(a.x[Ps + p], a.g.oy, a.g.inv_dx, ny, b[1], t[1]);
-    ok &= stencil_axis_joint(a.x[2 * Ps + p], a.g.oz, a.g.inv_dx, nz, b[2], t[2]);
-    if (!ok) raise_flag(a.status, kFlagRange);
-    ph = a.phase[p];
-    const bool ph_ok = ph == 0 || ph == 1;
-    if (!ph_ok) raise_flag(a.status, kFlagPhase);
-    valid = ok && ph_ok;
-    if (valid) m = a.mass_f[p] + (ph == 1 && a.mass_s ? a.mass_s[p] : 0.0f);
-  }
-  if (!valid) {
+  bool valid = false;
+  auto load = [&](int slot) {
+    const int64_t i = (int64_t)blockIdx.x * BS + slot;
+    valid = i < a.P;
+    p = 0;
     ph = 0;
-    b[0] = b[1] = b[2] = 0;
-    t[0] = t[1] = t[2] = 0.0f;
-  }
+    m = 0.0f;
+    if (valid) {
+      p = a.perm ? min(max(a.perm[i], 0), (int)(a.P - 1)) : (int)i;
+      bool ok = stencil_axis_joint(a.x[p], a.g.ox, a.g.inv_dx, nx, b[0], t[0]);
+      ok &= stencil_axis_joint(a.x[Ps + p], a.g.oy, a.g.inv_dx, ny, b[1], t[1]);
+      ok &= stencil_axis_joint(a.x[2 * Ps + p], a.g.oz, a.g.inv_dx, nz, b[2], t[2]);
+      if (!ok) raise_flag(a.status, kFlagRange);
+      ph = a.phase[p];
+      const bool ph_ok = ph == 0 || ph == 1;
+      if (!ph_ok) raise_flag(a.status, kFlagPhase);
+      valid = ok && ph_ok;
+      if (valid) m = a.mass_f[p] + (ph == 1 && a.mass_s ? a.mass_s[p] : 0.0f);
+    }
+    if (!valid) {
+      ph = 0;
+      b[0] = b[1] = b[2] = 0;
+      t[0] = t[1] = t[2] = 0.0f;
+    }
+  };
+  int slot = pair_slot<NW>(tid);
+  load(slot);
 
   // the brick node of this thread in every brick (it clears and flushes it)
   static_assert(kBrickNodes <= BS, "one brick node per thread");
@@ -77,14 +82,26 @@ __global__ __launch_bounds__(kMixBS, 4) void mixture_p2g_kernel(MixtureP2GArgs a
 #pragma unroll
     for (int k = 0; k < kMixK * kMixCh; ++k) brick[k * kMixV + own] = 0.0;
   }
-  const int seg = plan_bricks<BS, kMixK>(plan, seg_tile, tid, slot,
-                                         valid ? brick_tile_id(0, b[0], b[1], b[2]) : kNoTile);
+  int seg = plan_bricks<BS, kMixK, true>(plan, seg_tile, tid, slot,
+                                         valid ? brick_tile_id(0, b[0], b[1], b[2]) : kNoTile,
+                                         (uint32_t)((b[2] * 1024 + b[1]) * 1024 + b[0]));
+  // Chunks of dense cells fold quads, dealt out four slots to a quad: as pairs, two of a
+  // wavefront would share a cell and its LDS addresses (the positions are read again, from
+  // the caches; measured, pairs and quads, 2.35 M particles at 16 per cell: 27 modes 280 and
+  // 259 us, 4 modes 192 and 158; 1.5 M at 12: 177 and 166).
+  const int n_slots = (int)min((int64_t)BS, a.P - (int64_t)blockIdx.x * BS);
+  const bool quads = n_slots >= kMixQuadCell * plan_cells(plan);  // (uniform)
+  if (quads) {
+    slot = quad_slot<NW>(tid);
+    load(slot);
+    seg = brick_of_slot<BS, kMixK, true>(plan, slot);
+  }
   const bool lds = valid && seg >= 0 && seg < kMixK;
   // a pair folds when both lanes share stencil, brick and phase; every lane runs the
   // scatter below (an idle one with zero mass), since the folds read the partner lane
-  const PairFold pf = pair_fold_plan(valid ? ((ph << 30) | ((b[2] * 1024 + b[1]) * 1024 + b[0]))
-                                           : -1 - lane,
-                                     seg, valid, lane);
+  const int key = valid ? ((ph << 30) | ((b[2] * 1024 + b[1]) * 1024 + b[0])) : -1 - lane;
+  PairFold pf = pair_fold_plan(key, seg, valid, lane);
+  const float quad_f = quad_fold_plan(quads, key, seg, valid, lane, pf);
   {
     const Rows Rx = p2g_rows_scaled(basis_p2g(t[0]), m);
     const Rows Ry = p2g_rows_scaled(basis_p2g(t[1]), 1.0f);
@@ -101,6 +118,10 @@ __global__ __launch_bounds__(kMixBS, 4) void mixture_p2g_kernel(MixtureP2GArgs a
         float w[9];
 #pragma unroll
         for (int k = 0; k < 9; ++k) w[k] = pair_fold(v[k], pf.f);
+        if (quads) {
+#pragma unroll
+          for (int k = 0; k < 9; ++k) w[k] = quad_fold(w[k], quad_f);
+        }
         if (!pf.emit) return;
         if (lds) {
 #pragma unroll

@@ -129,3 +129,32 @@ def test_the_new_state_does_not_depend_on_the_lane_groups(n_modes):
         out.append([host(t).copy() for t in (ps.x_next, ps.coeff_next, ps.F_next, ps.mass_next)])
     for other in out[1:]:
         assert all(np.array_equal(a, b) for a, b in zip(out[0], other))
+
+
+@pytest.mark.parametrize("n_modes", [4, 27])
+@pytest.mark.parametrize("case", ["cross_cells", "dense_16", "dense_40", "mixed"])
+def test_mixture_scatter_at_pairs_and_quads(case, n_modes):
+    """The mixture P2G over cells on either side of the change to quads, both phases in the
+    same cells: each phase against the oracle's P2G of its particles."""
+    pp = require_gpu()
+    spec, x, c, _, _, _ = scene(case, None, 3, False)
+    P = x.shape[1]
+    note(f"mixture groups: {case} P={P} n_modes={n_modes}")
+    rng = np.random.default_rng(8)
+    phase = (rng.random(P) < 0.3).astype(np.int32)
+    mf, ms = rng.random((2, P)).astype(np.float32) + 0.5
+    g = pp.grid_from_spec(spec)
+    og = oracle_grid(g)
+    ps = pp.MixtureParticleSet(g, n_modes, dev(x), dev(c[:, :n_modes]), dev(phase, torch.int32),
+                               dev(mf), dev(ms), dt=1e-3)
+    ps.sort()
+    ps.p2g()
+    torch.cuda.synchronize()
+    assert ps.status_flags() == 0
+    N = g.nx * g.ny * g.nz
+    for k in range(2):
+        at = phase == k
+        m = (mf + ms if k else mf)[at]
+        M_ref, Q_ref = O.p2g(og, x[:, at], c[:, :n_modes][:, :, at], n_modes, m)
+        assert rel(host(ps.grid_mass).reshape(2, N)[k].reshape(M_ref.shape), M_ref) <= TOL_NORMWISE
+        assert rel(host(ps.grid_mom).reshape(2, 3 * N)[k].reshape(Q_ref.shape), Q_ref) <= TOL_NORMWISE
