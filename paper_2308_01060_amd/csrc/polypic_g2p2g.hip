@@ -49,7 +49,7 @@ __device__ __forceinline__ int fused_slot(int tid, int lg) {
 // the tiles of the new positions, such particles take a chunk past its bricks and go to
 // HBM, 27 atomics per channel each, and the call slows with the speed of the flow
 // (measured, 4.19 M particles, 4 modes, 0.1, 1.3 and 2.6 % of a cell per step and axis: 232,
-// 478 and 756 us; with these bricks 213, 249 and about 280).  The z stride spreads a half wavefront's
+// 478 and 756 us; with these bricks 215, 249 and 275).  The z stride spreads a half wavefront's
 // cells over the banks, as in the tile-only bricks.
 constexpr int kFuseN = kBrickN + 2;  // nodes per brick edge
 constexpr int kFuseSY = 8;
