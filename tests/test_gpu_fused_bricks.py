@@ -26,7 +26,10 @@ CASES = {
     "dense_16": (16, (6, 5, 7), 16, 0.9),            # quads
     "dense_40": (16, (3, 4, 3), 40, 0.5),
     "mixed": (24, (10, 10, 10), 11, 0.9),            # around the change to quads
+    "translate": (32, (10, 9, 10), 8, 0.6),          # and all by DRIFT: the bricks move along
+    "translate_dense": (32, (6, 5, 7), 16, 0.6),
 }
+DRIFT = (3.2, -4.7, 2.1)  # cells
 
 
 def scene(case, P, seed, mass_f):
@@ -63,6 +66,9 @@ def check(case, P, n_modes, mass_f, seed):
     ps.grid_update()
     # node velocities that move a particle by at most `move` per axis in dt = 1
     ps.grid_vel.uniform_(-move, move)
+    if case.startswith("translate"):
+        drift = torch.tensor(DRIFT, device="cuda")[:, None] / CASES[case][0]
+        ps.grid_vel.copy_((ps.grid_vel.reshape(3, -1) + drift).reshape(-1))
     ps.region_state.zero_()
     torch.cuda.synchronize()
     gv = host(ps.grid_vel).reshape(3, og.nz, og.ny, og.nx).astype(np.float64)
