@@ -38,10 +38,15 @@
  *             per-node quantities.
  * Stencil     Quadratic B-spline weights (section 3.1 leaves N(x) unnamed) over
  *             the 3x3x3 nodes b, b+1, b+2 per axis, where, in float32 with
- *             round-to-nearest and no contraction,
+ *             round-to-nearest,
  *                 u = (x - origin) * inv_dx,   b = floor(u - 1/2),   t = u - b - 1
- *             (t in [-1/2, 1/2) is the offset from the nearest node b + 1).  A
+ *             (t in [-1/2, 1/2] is the offset from the nearest node b + 1).  A
  *             particle is in range when 0 <= b <= n_axis - 3 on every axis.
+ *             The floor rounds u - 1/2 once (a fused multiply-add), in every call:
+ *             all agree on b where u lies within a rounding of a cell's border.
+ *             The last bit of t depends on the call: some subtract from the rounded
+ *             product, some fuse it.  With inv_dx a power of two the product is
+ *             exact and the two agree.
  * Modes       s_r = phi_kx(zx) phi_ky(zy) phi_kz(zz) evaluated at
  *             z = (x_i - x_p) / dx (the particle's current position; the affine
  *             map of Eq. 12 is not applied) with phi_0 = 1, phi_1 = z and

@@ -78,9 +78,14 @@ __host__ __device__ constexpr bool has_mode(int kx, int ky, int kz) {
 }
 
 // ---------------------------------------------------------------- stencil
-// u = (x - o) * inv_dx, b = floor(u - 1/2), t = u - b - 1, each a single
-// round-to-nearest float32 operation (t is exact).  Returns false when b is
+// u = (x - o) * inv_dx, b = floor(u - 1/2), t = u - b - 1 in float32.  Returns false when b is
 // outside [0, n - 3] (or the position is not finite).
+// The rounding intrinsics do not keep the compiler from contracting the product into either
+// subtraction.  As built, every kernel contracts it into the floor's, so that the sort's key,
+// the transfers and the range check agree on the base node of a position whose u lies within a
+// rounding of a cell's border; t's last bit differs (t - u is exact): the plain, staggered and
+// mixture G2P and the P2G adjoint subtract from the rounded product, the scatters and the G2P
+// adjoint contract it.
 __device__ __forceinline__ bool stencil_axis(float x, float o, float inv_dx, int n, int& b,
                                              float& t) {
   const float u = __fmul_rn(__fsub_rn(x, o), inv_dx);
@@ -91,18 +96,16 @@ __device__ __forceinline__ bool stencil_axis(float x, float o, float inv_dx, int
   return ok;
 }
 
-// The rounding intrinsics do not keep the compiler from contracting the product into either
-// subtraction, so the last bit of t (and ties of b) is the compiler's choice above.  Two
-// forms that are not, for kernels that need the offsets to the bit: the product apart, for
-// offsets computed in several places of a kernel; and the product contracted into both,
-// which is what the scatters do.  (Nodes that only a stencil's edge reaches have masses
-// down to the square of that last bit.)
+// The same with every rounding written out, for kernels that compute the offsets of one
+// position in several places: the floor contracted, as everywhere, and t from the rounded
+// product (apart, as the gathers) or contracted (joint, as the scatters).  (Nodes that only a
+// stencil's edge reaches have masses down to the square of that last bit.)
 __device__ __forceinline__ bool stencil_axis_apart(float x, float o, float inv_dx, int n, int& b,
                                                    float& t) {
 #pragma clang fp contract(off)
   const float d = x - o;
   const float u = d * inv_dx;
-  const float f = floorf(u - 0.5f);
+  const float f = floorf(fmaf(d, inv_dx, -0.5f));
   const bool ok = (f >= 0.0f) && (f <= (float)(n - 3));
   b = ok ? (int)f : 0;
   t = ok ? u - (f + 1.0f) : 0.0f;
