@@ -137,16 +137,16 @@ __device__ __forceinline__ PairFold pair_fold_plan(int key, int seg, bool scatte
   return pf;
 }
 
-// A quad whose pairs both fold and agree folds once more, if asked (uniform): its first
-// lane emits.  Returns the factor of the second fold.
-__device__ __forceinline__ float quad_fold_plan(bool quads, int key, int seg, bool scatters,
-                                                int lane, PairFold& pf) {
-  if (!quads) return 0.0f;
+// A quad whose pairs both fold and agree adds once more, if asked (uniform), in 64 bits: its
+// first lane emits its pair's value plus quad_other of it.  Returns that call's mask.
+__device__ __forceinline__ int quad_fold_plan(bool quads, int key, int seg, bool scatters, int lane,
+                                              PairFold& pf) {
+  if (!quads) return 0;
   const int pair = pf.f != 0.0f;
   const bool quad = pair && quad_swap_i(pair) != 0 && key == quad_swap_i(key) &&
                     seg == quad_swap_i(seg);
   if (quad) pf.emit = scatters && (lane & 3) == 0;
-  return quad ? 1.0f : 0.0f;
+  return quad ? ~0 : 0;
 }
 
 // Origin (first node) of the brick of tile `tl` along each axis, for bricks that start

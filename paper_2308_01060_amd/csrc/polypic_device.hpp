@@ -765,6 +765,16 @@ __device__ __forceinline__ float quad_fold(float v, float f) {
   return v;
 }
 
+// v of lane ^ 2 where `mask` is ~0, and 0 (whatever that lane holds, so no non-finite value
+// crosses over) where it is 0.
+__device__ __forceinline__ float quad_other(float v, int mask) {
+  float o;
+  asm volatile("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+               : "=v"(o)
+               : "v"(v), "v"(mask));
+  return o;
+}
+
 // ---------------------------------------------------------------- workgroup rows
 // Access to this thread's float of a workgroup's slice of a particle row, through
 // a buffer descriptor over the slice (its base and its n valid floats), which is

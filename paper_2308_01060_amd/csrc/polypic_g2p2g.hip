@@ -81,7 +81,10 @@ constexpr int kQuadCell = 10;  // particles per cell of a chunk from which quads
 // particles: 0.40 ms at 3 waves per SIMD, 0.38 ms at 4).  With at most 8 modes 28 KB and
 // fewer registers allow 5.
 // Lane groups: a group whose particles share brick and base node adds its node values
-// across lanes first, and one lane does the atomics.  Pairs do best while the 32 pairs of
+// across lanes first, and one lane does the atomics.  A pair adds in 32 bits, a quad's two
+// pairs in 64, as the bricks (their sums then hold the bits that pairs leave; measured, 32 and
+// 64 bits for the second sum, 4.19 M particles at 16 per cell: 4 modes 240 and 233 us, 27 modes
+// 387 and 398).  Pairs do best while the 32 pairs of
 // a wavefront fall in different cells (one DPP fold per node value instead of two); in
 // chunks whose cells hold more particles two pairs of a wavefront share a cell and its LDS
 // addresses, and quads do better.  Left to itself (lane_group 0) the kernel counts the
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   }
   const bool emit = valid && (quad ? (lane & 3) == 0 : (!pair || (lane & 1) == 0));
   const float pair_f = pair ? 1.0f : 0.0f;
-  const float quad_f = quad ? 1.0f : 0.0f;
+  const int quad_m = quad ? ~0 : 0;
   {
     const Rows Rx = p2g_rows_scaled(basis_p2g(u0), m);
     const Rows Ry = p2g_rows_scaled(basis_p2g(u1), 1.0f);
@@ -447,26 +450,35 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       return [=](int jz, float (&v)[9]) {
         float w[9];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-          w[k] = pair_fold(v[k], pair_f);
-        }
+        for (int k = 0; k < 9; ++k) w[k] = pair_fold(v[k], pair_f);
+        // rows [j0, j1) of the plane to the brick, or to HBM
+        auto put = [&](int j0, int j1, auto&& value) {
+          if (!emit) return;
+          if (lds) {
+#pragma unroll
+            for (int jy = j0; jy < j1; ++jy)
+#pragma unroll
+              for (int jx = 0; jx < 3; ++jx)
+                atomicAdd(lbc + jx + kFuseSY * jy + kFuseSZ * jz, value(jx + 3 * jy));
+          } else {
+#pragma unroll
+            for (int jy = j0; jy < j1; ++jy)
+#pragma unroll
+              for (int jx = 0; jx < 3; ++jx)
+                atomicAdd(gc + gbase + (jz * nxny + jy * nx + jx), (float)value(jx + 3 * jy));
+          }
+        };
         if (quads) {
+          // two pairs are added in 64 bits, as the bricks add; a row at a time, for the registers
 #pragma unroll
-          for (int k = 0; k < 9; ++k) w[k] = quad_fold(w[k], quad_f);
-        }
-        if (!emit) return;
-        if (lds) {
+          for (int jy = 0; jy < 3; ++jy) {
+            float other[3];  // (every lane)
 #pragma unroll
-          for (int jy = 0; jy < 3; ++jy)
-#pragma unroll
-            for (int jx = 0; jx < 3; ++jx)
-              atomicAdd(lbc + jx + kFuseSY * jy + kFuseSZ * jz, (double)w[jx + 3 * jy]);
+            for (int jx = 0; jx < 3; ++jx) other[jx] = quad_other(w[jx + 3 * jy], quad_m);
+            put(jy, jy + 1, [&](int k) { return (double)w[k] + (double)other[k - 3 * jy]; });
+          }
         } else {
-#pragma unroll
-          for (int jy = 0; jy < 3; ++jy)
-#pragma unroll
-            for (int jx = 0; jx < 3; ++jx)
-              atomicAdd(gc + gbase + (jz * nxny + jy * nx + jx), w[jx + 3 * jy]);
+          put(0, 3, [&](int k) { return (double)w[k]; });
         }
       };
     };

@@ -10,8 +10,9 @@
 // P2G: one thread per sorted slot; lane pairs take consecutive slots and the pairs of
 // a wavefront are spread over the workgroup's chunk.  FP64 LDS bricks of 6^3 nodes for
 // the first three distinct 4^3 tiles of the chunk -- fluid and solid particles of a tile
-// share its brick, two channels of either phase at a time -- take the node values, added first across a
-// pair with the same stencil and phase (one DPP fold each), one z plane at a time;
+// share its brick, two channels of either phase at a time -- take the node values, added first
+// across a pair with the same stencil and phase (one DPP fold each; in chunks of dense cells
+// two pairs more, in 64 bits), one z plane at a time;
 // one float atomic per non-zero brick value at the flush; other tiles add to HBM.
 // The nodal values are the separable three-stage contraction of the plain P2G.
 #include "polypic_bricks.hpp"
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(kMixBS, 4) void mixture_p2g_kernel(MixtureP2GArgs a
   // scatter below (an idle one with zero mass), since the folds read the partner lane
   const int key = valid ? ((ph << 30) | ((b[2] * 1024 + b[1]) * 1024 + b[0])) : -1 - lane;
   PairFold pf = pair_fold_plan(key, seg, valid, lane);
-  const float quad_f = quad_fold_plan(quads, key, seg, valid, lane, pf);
+  const int quad_m = quad_fold_plan(quads, key, seg, valid, lane, pf);
   {
     const Rows Rx = p2g_rows_scaled(basis_p2g(t[0]), m);
     const Rows Ry = p2g_rows_scaled(basis_p2g(t[1]), 1.0f);
@@ -118,23 +119,34 @@ __global__ __launch_bounds__(kMixBS, 4) void mixture_p2g_kernel(MixtureP2GArgs a
         float w[9];
 #pragma unroll
         for (int k = 0; k < 9; ++k) w[k] = pair_fold(v[k], pf.f);
+        // rows [j0, j1) of the plane to the brick, or to HBM
+        auto put = [&](int j0, int j1, auto&& value) {
+          if (!pf.emit) return;
+          if (lds) {
+#pragma unroll
+            for (int jy = j0; jy < j1; ++jy)
+#pragma unroll
+              for (int jx = 0; jx < 3; ++jx)
+                atomicAdd(lbc + jx + kMixSY * jy + kMixSZ * jz, value(jx + 3 * jy));
+          } else {
+#pragma unroll
+            for (int jy = j0; jy < j1; ++jy)
+#pragma unroll
+              for (int jx = 0; jx < 3; ++jx)
+                atomicAdd(gc + jx + sy * jy + sz * jz, (float)value(jx + 3 * jy));
+          }
+        };
         if (quads) {
+          // two pairs are added in 64 bits, as the bricks add; a row at a time, for the registers
 #pragma unroll
-          for (int k = 0; k < 9; ++k) w[k] = quad_fold(w[k], quad_f);
-        }
-        if (!pf.emit) return;
-        if (lds) {
+          for (int jy = 0; jy < 3; ++jy) {
+            float other[3];  // (every lane)
 #pragma unroll
-          for (int jy = 0; jy < 3; ++jy)
-#pragma unroll
-            for (int jx = 0; jx < 3; ++jx)
-              atomicAdd(lbc + jx + kMixSY * jy + kMixSZ * jz, (double)w[jx + 3 * jy]);
+            for (int jx = 0; jx < 3; ++jx) other[jx] = quad_other(w[jx + 3 * jy], quad_m);
+            put(jy, jy + 1, [&](int k) { return (double)w[k] + (double)other[k - 3 * jy]; });
+          }
         } else {
-#pragma unroll
-          for (int jy = 0; jy < 3; ++jy)
-#pragma unroll
-            for (int jx = 0; jx < 3; ++jx)
-              atomicAdd(gc + jx + sy * jy + sz * jz, w[jx + 3 * jy]);
+          put(0, 3, [&](int k) { return (double)w[k]; });
         }
       };
     };
