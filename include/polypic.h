@@ -488,10 +488,10 @@ int32_t polypic_mac_g2p(const polypic_grid* grid, int64_t P, int32_t n_modes, fl
 
 /* Launch choice of polypic_g2p2g per mode count:
  *   lane_group: the number of particles of consecutive sorted slots whose node
- *     values are added across lanes before one brick atomic (2 or 4).  The lanes'
- *     groups are spread over the workgroup's chunk 8 or 16 slots apart, so 4
- *     suits about 12 particles per cell and more.  By default (reported as 2) each
- *     chunk of 256 slots takes 2, or 4 where its cells hold 10 or more on average.
+ *     values are added across lanes before one brick atomic.  2 (the default): two,
+ *     and four in every chunk of 256 slots whose cells hold 10 particles or more on
+ *     average.  4: four in every chunk.  Two values are added in 32 bits, the sums
+ *     of two pairs in 64, as the workgroup's sums.
  *   schedule: the order in which workgroups take the chunks of slots,
  *     POLYPIC_SCHED_LINEAR (the default: in launch order) or POLYPIC_SCHED_XCD
  *     (each XCD takes a contiguous eighth, so that neighbouring chunks, which
@@ -502,7 +502,8 @@ int32_t polypic_mac_g2p(const polypic_grid* grid, int64_t P, int32_t n_modes, fl
  * keeps the fastest for later calls at this mode count and writes it to
  * *lane_group_out and *schedule_out (either may be NULL); the outputs are those of
  * a final run with the choice.  The choice changes only the order of the grid
- * sums.  (polypic_batch_g2p2g uses the default groups in the XCD order.) */
+ * sums.  Setting what polypic_get_g2p2g_config returned changes nothing.
+ * (polypic_batch_g2p2g uses the default groups in the XCD order.) */
 int32_t polypic_set_g2p2g_config(int32_t n_modes, int32_t lane_group, int32_t schedule);
 int32_t polypic_get_g2p2g_config(int32_t n_modes, int32_t* lane_group, int32_t* schedule);
 int32_t polypic_autotune_g2p2g(const polypic_grid* grid, int64_t P, int32_t n_modes, float dt,

@@ -113,8 +113,10 @@ P2GConfig to_config(const P2GChoice& c) {
 }
 
 std::atomic<int> g_g2p_sched{POLYPIC_SCHED_LINEAR};
-// lane-group size of the fused G2P2G kernel per mode count (0: the default, by each
-// chunk's cells, reported as pairs)
+// lane groups of the fused G2P2G kernel per mode count: 4, quads in every chunk; 2 (and 0, as
+// initialised), the default, pairs or quads by each chunk's cells.  One value for what get
+// reports and what set stores: a caller that restores a setting restores the default too, and
+// the autotuner's candidates hold it.
 std::atomic<int> g_fused_lane[28];
 std::atomic<int> g_fused_sched[28];  // POLYPIC_SCHED_LINEAR (the default) or _XCD
 
@@ -987,7 +989,7 @@ int32_t polypic_g2p2g(const polypic_grid* grid, int64_t P, int32_t n_modes, floa
   a.gp2 = grid_mom + 2 * N;
   a.status = status_dev;
   a.gstride = N;
-  a.lane_group = g_fused_lane[n_modes].load();
+  a.lane_group = fused_lane_group(n_modes);
   a.accumulate = accumulate != 0;
   a.sched = fused_sched(n_modes);
   a.regions = region_state;
@@ -1001,7 +1003,7 @@ int32_t polypic_set_g2p2g_config(int32_t n_modes, int32_t lane_group, int32_t sc
   if (lane_group != -1 && lane_group != 2 && lane_group != 4) return POLYPIC_EINVAL;
   if (schedule != -1 && schedule != POLYPIC_SCHED_LINEAR && schedule != POLYPIC_SCHED_XCD)
     return POLYPIC_EINVAL;
-  g_fused_lane[n_modes].store(lane_group == -1 ? 0 : lane_group);
+  g_fused_lane[n_modes].store(lane_group == -1 ? 2 : lane_group);
   g_fused_sched[n_modes].store(schedule == -1 ? POLYPIC_SCHED_LINEAR : schedule);
   return POLYPIC_OK;
 }
@@ -1423,7 +1425,7 @@ int32_t polypic_batch_g2p2g(const polypic_batch* batch, int32_t n_modes, float d
   // cache between the passes, so neighbouring chunks share one L2 (measured, 64
   // scenes, 25.7 M particles: 3.81 -> 3.57 ms per graph step)
   a.sched = kSchedXcd;
-  a.lane_group = 0;
+  a.lane_group = 2;
   discard_stale_error();
   return from_hip(launch_g2p2g_batch(a, batch_table(batch), batch->n_scenes, n_modes,
                                      (hipStream_t)stream));

@@ -87,7 +87,7 @@ constexpr int kQuadCell = 10;  // particles per cell of a chunk from which quads
 // 387 and 398).  Pairs do best while the 32 pairs of
 // a wavefront fall in different cells (one DPP fold per node value instead of two); in
 // chunks whose cells hold more particles two pairs of a wavefront share a cell and its LDS
-// addresses, and quads do better.  Left to itself (lane_group 0) the kernel counts the
+// addresses, and quads do better.  By default (lane_group 2) the kernel counts the
 // cells of each chunk and takes quads from kQuadCell particles per cell on (measured, pairs
 // and quads, 27 modes: 194 and 207 us at 8 per cell, 330 and 323 at 12, 457 and 419 at 16;
 // 4 modes: 238 and 203 at 12, 330 and 251 at 16).
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   bool gather = in && ok;
   cell_of[slot] = gather ? (uint32_t)b0 | ((uint32_t)b1 << 10) | ((uint32_t)b2 << 20) : kNoCell;
   float* const stage = reinterpret_cast<float*>(lds_all) + kStage0;
-  if (a.lane_group == 0) {  // (in case the slots are dealt out again)
+  if (lg == 1) {  // (in case the slots are dealt out again)
     stage[slot] = xp[0];
     stage[BS + slot] = xp[1];
     stage[2 * BS + slot] = xp[2];
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       run_head[run] = (int16_t)tid;
     }
   }
-  if (a.lane_group == 0 && n_slots >= kQuadCell * cells) {  // (uniform)
+  if (lg == 1 && n_slots >= kQuadCell * cells) {  // (uniform)
     lg = 2;
     slot = fused_slot<NW>(tid, lg);
     in = slot < n_slots;

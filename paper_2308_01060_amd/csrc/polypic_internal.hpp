@@ -177,7 +177,7 @@ struct G2P2GArgs {
   float* gp2;
   int32_t* status;
   int64_t gstride;       // channel stride of gv
-  int lane_group;        // particles folded per brick atomic: 2 or 4, 0: by the chunk's cells
+  int lane_group;        // 4: quads in every chunk, else pairs or quads by its cells
   int accumulate;        // 1: add to the grid as it is (the caller cleared it)
   int sched;             // chunk order: kSchedLinear or kSchedXcd
   uint32_t* regions;     // region flags to set where the scatter lands (or nullptr)

@@ -436,15 +436,15 @@ def polypic_g2p2g(grid: polypic_grid, n_modes: int, dt: float, grid_vel: torch.T
 
 
 class FusedChoice(NamedTuple):
-    """Launch choice of polypic_g2p2g: lane-group size and chunk order (POLYPIC_SCHED_*)."""
+    """Launch choice of polypic_g2p2g: lane groups (2 or 4) and chunk order (POLYPIC_SCHED_*)."""
 
     lane_group: int
     schedule: int
 
 
 def polypic_set_g2p2g_config(n_modes: int, lane_group: int = -1, schedule: int = -1) -> None:
-    """Lane-group size (2 or 4) and chunk order (POLYPIC_SCHED_LINEAR or _XCD) of
-    polypic_g2p2g at this mode count; -1 for a default."""
+    """Lane groups (2: pairs, and quads in chunks of dense cells; 4: quads throughout) and chunk
+    order (POLYPIC_SCHED_LINEAR or _XCD) of polypic_g2p2g at this mode count; -1 for a default."""
     check(_lib.load().polypic_set_g2p2g_config(int(n_modes), int(lane_group), int(schedule)),
           "polypic_set_g2p2g_config")
 
@@ -465,7 +465,7 @@ def polypic_autotune_g2p2g(grid: polypic_grid, n_modes: int, dt: float, grid_vel
                            mass_in: Optional[torch.Tensor] = None,
                            mass_out: Optional[torch.Tensor] = None,
                            uniform_mass: float = 1.0) -> FusedChoice:
-    """Times polypic_g2p2g with lane groups of 2 and 4, in launch and in XCD chunk order, on
+    """Times polypic_g2p2g with the lane groups 2 and 4, in launch and in XCD chunk order, on
     these arguments (synchronises), keeps the fastest for this mode count and returns it;
     the outputs are the call's."""
     P = x_in.numel() // 3

@@ -89,3 +89,42 @@ def test_a_nan_stays_with_its_cell(call, n_modes):
     at = M != 0
     assert rel(gm[at], M[at]) <= 1e-6
     assert rel(gp[:, at], Q[:, at]) <= 1e-6
+
+
+@pytest.mark.parametrize("put_back", [False, True])
+def test_a_setting_read_and_put_back_keeps_the_default(put_back):
+    """The default takes quads in chunks of dense cells, and so does the setting that get reports
+    for it: 16 per cell, 1 mode, where pairs throughout take 1.3 times as long (1.2 asked)."""
+    pp = require_gpu()
+    ops = pp.ops
+    note(f"group setting read and put back: {put_back}")
+    n, ppc, m = 64, 16, 1
+    rng = torch.Generator("cuda").manual_seed(3)
+    cells = torch.cartesian_prod(*[torch.arange(40, device="cuda")] * 3).t().repeat_interleave(
+        ppc, 1)
+    P = cells.shape[1]
+    x = (12.0 + cells + torch.rand(3, P, device="cuda", generator=rng)) / n
+    ps = pp.ParticleSet(pp.make_grid((n + 4,) * 3, 1.0 / n), m, x,
+                        torch.zeros(3, m, P, device="cuda"), dt=0.0)
+    ps.sort()
+
+    def ms(lane_group):
+        ops.polypic_set_g2p2g_config(m, lane_group, -1)
+        t = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ps.g2p2g()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return sorted(t)[4]
+
+    try:
+        ms(-1)
+        got = ops.polypic_get_g2p2g_config(m)
+        again = got.lane_group if put_back else -1
+        assert ms(again) <= 1.2 * ms(-1)
+        assert ms(again) <= 1.2 * ms(4)
+    finally:
+        ops.polypic_set_g2p2g_config(m, -1, -1)
