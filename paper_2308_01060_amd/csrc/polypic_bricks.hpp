@@ -142,9 +142,13 @@ __device__ __forceinline__ PairFold pair_fold_plan(int key, int seg, bool scatte
 __device__ __forceinline__ int quad_fold_plan(bool quads, int key, int seg, bool scatters, int lane,
                                               PairFold& pf) {
   if (!quads) return 0;
+  // every lane runs the exchanges: whether a pair belongs together differs between the two pairs
+  // of a quad, and a DPP read of a lane that does not execute it leaves the reader's register as
+  // it was
   const int pair = pf.f != 0.0f;
-  const bool quad = pair && quad_swap_i(pair) != 0 && key == quad_swap_i(key) &&
-                    seg == quad_swap_i(seg);
+  const int other_pair = quad_swap_i(pair), other_key = quad_swap_i(key);
+  const int other_seg = quad_swap_i(seg);
+  const bool quad = pair && other_pair != 0 && key == other_key && seg == other_seg;
   if (quad) pf.emit = scatters && (lane & 3) == 0;
   return quad ? ~0 : 0;
 }

@@ -91,6 +91,30 @@ def test_a_nan_stays_with_its_cell(call, n_modes):
     assert rel(gp[:, at], Q[:, at]) <= 1e-6
 
 
+@pytest.mark.parametrize("n_modes", [1, 4, 8, 27])
+@pytest.mark.parametrize("base", [(1, 0, 0), (0, 0, 0), (5, 2, 1)])
+def test_a_pair_beside_two_single_lanes(base, n_modes):
+    """Four slots of the mixture P2G (in the caller's order) that hold two particles of one cell
+    and one each of two other cells, in a chunk of dense cells, in its second tile: the pair is
+    added by itself.  (Base node (1, 0, 0) in the second brick is where a lane that reads its own
+    register in place of an idle neighbour's finds its own cell and brick.)"""
+    pp = require_gpu()
+    note(f"group sums: pair and singles at {base}, n_modes={n_modes}")
+    at = lambda b: (np.array(b, np.float32) + np.float32(1.0)) / N  # noqa: E731
+    far, one, two = (20, 20, 20), (9, 9, 9), (17, 9, 9)
+    cells = [far] * 128 + [base, base, one, two] + [one] * 124
+    x = np.ascontiguousarray(np.stack([at(b) for b in cells], 1).astype(np.float32))
+    rng = np.random.default_rng(4)
+    c = rng.standard_normal((3, n_modes, 256)).astype(np.float32)
+    mass = (0.5 + rng.random(256)).astype(np.float32)
+    og, gm, gp, _ = scatter(pp, "mixture", n_modes, x, mass, c)
+    M, Q = O.p2g(og, x, c, n_modes, mass)
+    assert rel(gm, M) <= 1e-5
+    here = tuple(slice(v, v + 3) for v in base[::-1])
+    assert rel(gm[here], M[here]) <= 1e-6
+    assert rel(gp[(slice(None),) + here], Q[(slice(None),) + here]) <= 1e-5
+
+
 @pytest.mark.parametrize("put_back", [False, True])
 def test_a_setting_read_and_put_back_keeps_the_default(put_back):
     """The default takes quads in chunks of dense cells, and so does the setting that get reports
