@@ -115,6 +115,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   __shared__ int16_t run_head[kRuns];   // first slot of the runs, then of the bricks
   __shared__ int origin[K][3];          // first base node of the bricks
   __shared__ int n_distinct;
+  __shared__ int n_astray;              // some slot has no brick in place
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -149,6 +150,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   ok &= stencil_axis_apart(xp[1], g.oy, g.inv_dx, ny, b1, t1);
   ok &= stencil_axis_apart(xp[2], g.oz, g.inv_dx, nz, b2, t2);
   if (in && !ok) raise_flag(a.status, kFlagRange);
+  if (tid == 0) n_astray = 0;
   bool gather = in && ok;
   cell_of[slot] = gather ? (uint32_t)b0 | ((uint32_t)b1 << 10) | ((uint32_t)b2 << 20) : kNoCell;
   float* const stage = reinterpret_cast<float*>(lds_all) + kStage0;
@@ -361,58 +363,117 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   }
   if (!valid) m = 0.0f;
   const int run_slot = run_of[slot];
-  // brick of this slot's run.  A run past kRuns keeps a value of its own (K + run index,
-  // above every distinct-tile index d < kRuns), so that two lanes of different runs never
-  // compare equal below.
+  // brick of this slot's run: the tile's index among the distinct ones
   const bool dedup = n_runs > K;  // (uniform)
-  const int seg = run_slot < 0 || !dedup ? run_slot
-                  : run_slot < kRuns     ? run_brick[run_slot]
-                                         : K + run_slot;
-  const int nb = dedup ? min(n_distinct, K) : n_runs;
+  const int seg = run_slot < 0 || !dedup ? run_slot : run_slot < kRuns ? run_brick[run_slot] : K;
+  int nb = dedup ? min(n_distinct, K) : n_runs;
   // this thread's nodes of every brick (it clears and flushes them)
   constexpr int kOwn = kFuseNodes / BS;
   static_assert(kOwn * BS == kFuseNodes, "whole nodes per thread");
   const int own_x = tid & 7, own_y = (tid >> 3) & 7, own_z = tid >> 6;  // z: + q * BS / 64
   const int own_lds = own_x + kFuseSY * own_y + kFuseSZ * own_z;
-  for (int k = 0; k < nb * kFuseCh; ++k)
+  auto clear_bricks = [&](int k0, int k1) {
+    for (int k = k0; k < k1; ++k)
 #pragma unroll
-    for (int q = 0; q < kOwn; ++q) brick[k * kFuseV + own_lds + q * (BS / 64) * kFuseSZ] = 0.0;
-  // A brick's first base node is one below its tile, moved by what the tile's first slot
-  // moved where that is more than a cell: a flow of several cells per step moves a tile's
-  // particles alike (measured, 4.19 M particles, 4 modes, a smooth flow of 1.3 and 3.8 cells
-  // per step and axis: 919 and 2980 us; with the bricks left in place 2418 and 10623, with
-  // bricks of the new positions' tiles 6096 and 7497).
-  const uint32_t tl = tile_bits(cell_of[slot]);
-  if (seg >= 0 && seg < K && slot == run_head[seg]) {
-    auto moved = [&](int now, int before) {
-      const int d = valid ? now - before : 0;
-      return d < -1 || d > 1 ? d : 0;
-    };
-    const uint32_t cell = cell_of[slot];
-    origin[seg][0] = (int)(tl & 1023u) - 1 + moved(c0, (int)(cell & 1023u));
-    origin[seg][1] = (int)((tl >> 10) & 1023u) - 1 + moved(c1, (int)((cell >> 10) & 1023u));
-    origin[seg][2] = (int)((tl >> 20) & 1023u) - 1 + moved(c2, (int)((cell >> 20) & 1023u));
+      for (int q = 0; q < kOwn; ++q) brick[k * kFuseV + own_lds + q * (BS / 64) * kFuseSZ] = 0.0;
+  };
+  clear_bricks(0, nb * kFuseCh);
+  // in place, a brick's first base node is one below its tile
+  const uint32_t cell = cell_of[slot], tl = tile_bits(cell);
+  int w0 = (int)(tl & 1023u) - 1, w1 = (int)((tl >> 10) & 1023u) - 1, w2 = (int)(tl >> 20) - 1;
+  auto inside = [&](int o0, int o1, int o2) {
+    return max(max((unsigned)(c0 - o0), (unsigned)(c1 - o1)), (unsigned)(c2 - o2)) <
+           (unsigned)(kFuseN - 2);
+  };
+  int my_brick = gather && seg >= 0 && seg < K && inside(w0, w1, w2) ? seg : -1;
+  const bool heads = gather && seg >= 0 && seg < K && slot == run_head[seg];
+  if (heads) {
+    origin[seg][0] = w0;
+    origin[seg][1] = w1;
+    origin[seg][2] = w2;
   }
+  if (__ballot(gather && my_brick < 0) != 0ull && lane == 0) n_astray = 1;
   __syncthreads();  // the bricks are clear and placed
-  // the new base node in its brick; a slot without a brick, or that moved past it, goes to HBM
-  const int my_brick = gather && seg >= 0 && seg < K ? seg : -1;
-  const int w0 = my_brick >= 0 ? origin[my_brick][0] : c0;
-  const int w1 = my_brick >= 0 ? origin[my_brick][1] : c1;
-  const int w2 = my_brick >= 0 ? origin[my_brick][2] : c2;
-  const bool lds = my_brick >= 0 && (unsigned)(c0 - w0) < (unsigned)kBrickN &&
-                   (unsigned)(c1 - w1) < (unsigned)kBrickN &&
-                   (unsigned)(c2 - w2) < (unsigned)kBrickN;
+  const bool astray = __builtin_amdgcn_readfirstlane(n_astray) != 0;  // (uniform)
+  if (astray) {
+    // Some slot left its brick, or is past the bricks.  The bricks are then placed anew, one
+    // after the other, each on the candidate that holds most of the slots left: the bricks in
+    // place, and the tiles of eight slots of the chunk moved as those slots moved.  A flow of
+    // several cells per step moves a tile's particles alike; a splash or a jet moves a few of
+    // them, and the others are to stay in their brick (measured, 4.19 M particles, 4 modes, 192
+    // us at rest: a smooth flow of 1.3 cells per step and axis 454 us; the first cell of every
+    // tile moved 3 and 6 cells 257 and 303, all others moved so 266 and 288.  With bricks moved
+    // by their tile's first slot 1640; 1358 and 2812, 1528 and 2495.  With bricks on the tiles
+    // of the new positions 6443; 273 and 637, 638 and 922).
+    constexpr int kSample = BS / 8, kCand = 8 + K;
+    static_assert(kCand <= 16 && 16 * K <= kRuns, "votes of each brick in run_brick");
+    auto pack = [](int o0, int o1, int o2) {  // (a brick that starts below the grid starts on it)
+      return (uint32_t)max(o0, 0) | (uint32_t)max(o1, 0) << 10 | (uint32_t)max(o2, 0) << 20;
+    };
+    if (slot % kSample == 0)
+      run_tile[slot / kSample] =
+          gather ? pack(c0 - 1 - (int)(cell & 3u), c1 - 1 - (int)((cell >> 10) & 3u),
+                        c2 - 1 - (int)((cell >> 20) & 3u))
+                 : kNoCell;
+    if (heads) run_tile[8 + seg] = pack(w0, w1, w2);
+    if (tid >= nb && tid < K) run_tile[8 + tid] = kNoCell;
+    if (tid < 16 * K) run_brick[tid] = 0;
+    clear_bricks(nb * kFuseCh, K * kFuseCh);
+    __syncthreads();
+    const int cand = (int)run_tile[lane & 15];
+    uint32_t fits = 0;  // candidates that hold this slot
+#pragma unroll
+    for (int j = 0; j < kCand; ++j) {
+      const uint32_t o = (uint32_t)__builtin_amdgcn_readlane(cand, j);
+      if (o != kNoCell && inside((int)(o & 1023u), (int)((o >> 10) & 1023u), (int)(o >> 20)))
+        fits |= 1u << j;
+    }
+    if (!gather) fits = 0;
+    my_brick = -1;
+    for (nb = 0; nb < K; ++nb) {
+      const uint32_t left = my_brick < 0 ? fits : 0u;
+      int votes = 0;  // of this wavefront, for candidate `lane`
+#pragma unroll
+      for (int j = 0; j < kCand; ++j) {
+        const int n = __popcll(__ballot((left >> j) & 1u));
+        votes = lane == j ? n : votes;
+      }
+      if (votes != 0) atomicAdd(&run_brick[16 * nb + lane], votes);
+      __syncthreads();
+      int most = run_brick[16 * nb + (lane & 15)] << 4 | (15 - (lane & 15));
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) most = max(most, __shfl_xor(most, off, kWave));
+      most = __builtin_amdgcn_readfirstlane(most);
+      if (most >> 4 == 0) break;  // (uniform) none left that a candidate holds
+      const int best = 15 - (most & 15);
+      const uint32_t o = (uint32_t)__builtin_amdgcn_readlane(cand, best);
+      if ((left >> best) & 1u) {
+        my_brick = nb;
+        w0 = (int)(o & 1023u);
+        w1 = (int)((o >> 10) & 1023u);
+        w2 = (int)(o >> 20);
+      }
+      if (tid == 0) {
+        origin[nb][0] = (int)(o & 1023u);
+        origin[nb][1] = (int)((o >> 10) & 1023u);
+        origin[nb][2] = (int)(o >> 20);
+      }
+    }
+  }
+  const bool lds = my_brick >= 0;  // (a slot without a brick goes to HBM)
   if (a.regions) {
     // the regions the scatter lands in: the 6^3 nodes of each brick's tile, and those of
     // the new tile of every slot that left its tile or went to HBM (a box holding its
-    // stencil); before the scatter holds its node values (plain stores)
-    if (tid < 8 * nb) {
+    // stencil), of every slot when bricks were placed anew; before the scatter holds its node
+    // values (plain stores)
+    if (!astray && tid < 8 * nb) {
       const uint32_t tc = run_tile[tid >> 3];
       flag_box_corner(a.regions, g.region_off, (uint32_t)ck.s, nx, ny, nz,
                       (int)(tc & 1023u), (int)((tc >> 10) & 1023u),
                       (int)(tc >> 20), kBrickN, tid & 7);
     }
-    if (valid && (!lds || tile_bits((uint32_t)c0 | ((uint32_t)c1 << 10) | ((uint32_t)c2 << 20)) != tl)) {
+    if (valid && (astray || !lds ||
+                  tile_bits((uint32_t)c0 | ((uint32_t)c1 << 10) | ((uint32_t)c2 << 20)) != tl)) {
 #pragma unroll
       for (int corner = 0; corner < 8; ++corner)
         flag_box_corner(a.regions, g.region_off, (uint32_t)ck.s, nx, ny, nz, c0 & ~(kBrickT - 1),
@@ -420,16 +481,15 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     }
   }
   // the lane pair (lane ^ 1), and with quads the other pair of the quad, share this
-  // lane's segment and base node: every lane runs the exchanges (an invalid one with
-  // zero mass), since a DPP read from a lane that did not execute it is undefined
+  // lane's base node (which its brick holds as well): every lane runs the exchanges (an
+  // invalid one with zero mass), since a DPP read from a lane that did not execute it is
+  // undefined
   const int mykey = valid ? ((c2 * 1024 + c1) * 1024 + c0) : -1 - lane;
-  const int pair_key = pair_swap_i(mykey), pair_seg = pair_swap_i(seg);
-  const bool pair = mykey == pair_key && seg == pair_seg;
+  const bool pair = mykey == pair_swap_i(mykey);
   bool quad = false;
   if (quads) {
     const int quad_pair = quad_swap_i((int)pair), quad_key = quad_swap_i(mykey);
-    const int quad_seg = quad_swap_i(seg);
-    quad = pair && quad_pair != 0 && mykey == quad_key && seg == quad_seg;
+    quad = pair && quad_pair != 0 && mykey == quad_key;
   }
   const bool emit = valid && (quad ? (lane & 3) == 0 : (!pair || (lane & 1) == 0));
   const float pair_f = pair ? 1.0f : 0.0f;
@@ -440,7 +500,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     const Rows Rz = p2g_rows_scaled(basis_p2g(u2), 1.0f);
     const int lbase = (c0 - w0) + kFuseSY * (c1 - w1) + kFuseSZ * (c2 - w2);
     const int64_t gbase = g.node_off + (int64_t)(c2 * ny + c1) * nx + c0;
-    double* const lb = brick + (lds ? seg * kFuseCh * kFuseV + lbase : 0);
+    double* const lb = brick + (lds ? my_brick * kFuseCh * kFuseV + lbase : 0);
     // one plane of 9 node values at a time: the folds run on every lane, then a
     // single predicated block per plane does the atomics
     auto emitter = [&](int ch) {
