@@ -29,16 +29,32 @@ namespace {
 // Slot of a thread: lane groups of 2^lg consecutive slots (which in cell order
 // usually share a cell, hence a base node), the groups of a wavefront spread over
 // the workgroup's chunk so that they sit in different cells and their brick
-// atomics do not collide.  The wavefronts' places rotate from one 64 slots to the
-// next: the slots of a wavefront then differ modulo 64, and its writes to a staging
-// row (one float per slot, in slot order) fall in 64 distinct LDS banks.
-template <int NW>
+// atomics do not collide.
+// Output rows are staged in LDS, one float per slot, and 64 lanes of a wavefront must
+// write 64 distinct banks.  kRotate (rows that leave in whole lines, from a stage in slot
+// order): the wavefronts' places rotate from one 64 slots to the next, so that the
+// slots of a wavefront differ modulo 64.  Where a place steps back, two groups of a
+// wavefront come close to each other and may share a cell, so rows that leave slot by
+// slot keep the places and permute the stage instead (stage_pos; measured, at rest, 4.19 M
+// particles, rotated and permuted: 1, 4 and 8 modes 174, 187 and 198 us, 171, 184 and 195).
+template <int NW, bool kRotate>
 __device__ __forceinline__ int fused_slot(int tid, int lg) {
   static_assert(NW == 4, "four wavefronts' groups of 2 or 4 lanes: 64 slots per 16 >> lg groups");
   const int lane = tid & (kWave - 1);
   const int wv = tid / kWave;
   const int group = lane >> lg;
-  return ((group * NW + ((wv + (group >> (4 - lg))) & (NW - 1))) << lg) | (lane & ((1 << lg) - 1));
+  const int place = kRotate ? (wv + (group >> (4 - lg))) & (NW - 1) : wv;
+  return ((group * NW + place) << lg) | (lane & ((1 << lg) - 1));
+}
+
+// Position of slot s in a staging row (a permutation of each 32 slots) where the places do
+// not rotate.  The 64 slots one wavefront writes agree in their wavefront-index bits (lg,
+// lg + 1) and differ in bits 5-7, which a plain index drops from the bank number.  XORing bit
+// 6, and bits 5 ^ 7, into the wavefront-index bits puts the writes of each half wavefront on
+// 32 distinct banks and those of the whole wavefront on 64, while a read of 64 consecutive
+// slots only permutes each half.
+__device__ __forceinline__ int stage_pos(int s, int lg) {
+  return s ^ (((s >> 6) & 1) << lg) ^ ((((s >> 7) ^ (s >> 5)) & 1) << (lg + 1));
 }
 
 // Bricks of the scatter.  A workgroup's slots are in the order of the positions before
@@ -56,13 +72,17 @@ constexpr int kFuseSY = 8;
 constexpr int kFuseSZ = 68;
 constexpr int kFuseV = (kFuseN - 1) * (1 + kFuseSY + kFuseSZ) + 1;  // doubles per channel
 constexpr int kFuseNodes = kFuseN * kFuseN * kFuseN;
-// Channels a round of the scatter fills: two rounds of two channels let three bricks fit
-// where all four channels at once would leave two, and a chunk of a block's edge or of a
+// A round of the scatter fills two channels: two rounds let three bricks fit where all four
+// channels at once would leave two, and a chunk of a block's edge or of a
 // small scene touches three or four tiles (of a 16^3-cell block's slots, 4.5 % lie in the
 // third tile of their chunk or later, 0.9 % in the fourth or later).
-constexpr int kFuseCh = 2;
 constexpr int kFuseK = 3;  // bricks per workgroup
-constexpr int kFuseBrickF = (2 * kFuseK * kFuseCh * kFuseV + 63) / 64 * 64;  // in floats
+// All four channels of one brick fit in two rounds' space of three: a chunk of one brick (a
+// dense block at rest is mostly such chunks) takes one round (measured, at rest, 4.19 M
+// particles, two rounds and one: 1, 4 and 8 modes 180, 193 and 206 us, 175, 188 and 201).
+constexpr int kFusePool = 2 * kFuseK;  // channels of bricks that the LDS holds
+constexpr int kFuseOneRound = kFusePool / 4;  // bricks that fit with all four channels
+constexpr int kFuseBrickF = (2 * kFusePool * kFuseV + 63) / 64 * 64;  // in floats
 // Coefficients of the last component that the second half reads back from the LDS rows
 // they were staged in, instead of holding them in registers across the scatter of the
 // other channels: at 27 modes the 128 registers of 4 waves per SIMD otherwise spill, and
@@ -70,7 +90,6 @@ constexpr int kFuseBrickF = (2 * kFuseK * kFuseCh * kFuseV + 63) / 64 * 64;  // 
 // 11 spilled registers, 385 at none; 776 and 718 for a batch of 6 M particles).
 template <int NR>
 constexpr int kFuseKept = NR > 8 ? 12 : 0;
-constexpr int kRuns = kWave;  // runs of equal tiles looked at per workgroup
 constexpr uint32_t kNoCell = 0xFFFFFFFFu;
 // first node of the 4^3 tile of a packed base node (10 bits an axis)
 __device__ __forceinline__ uint32_t tile_bits(uint32_t cell) { return cell & 0x3FCFF3FCu; }
@@ -100,6 +119,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   constexpr int NW = BS / kWave;
   constexpr int K = kFuseK;
   constexpr int kKept = kFuseKept<NR>;
+  constexpr bool kRotate = kRowMode != kBySlot;
   static_assert(!Scenes::kMany, "a workgroup's slots lie in one scene (OneScene, SceneChunks)");
   constexpr int kRows = NR + 1 > 10 ? NR + 1 : 10;  // staged: a component, or F and the mass
   constexpr int kStage0 =  // floats
@@ -110,12 +130,14 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   __shared__ uint32_t cell_of[BS];  // by slot: base node before the advection, 10 bits an axis
   __shared__ int16_t run_of[BS];    // by slot: its run of equal tiles
   __shared__ int wave_heads[NW];    // heads of runs, and of cells << 16
-  __shared__ uint32_t run_tile[kRuns];  // tiles of the first runs, then of the bricks
-  __shared__ int run_brick[kRuns];      // brick (distinct-tile index) of each run
-  __shared__ int16_t run_head[kRuns];   // first slot of the runs, then of the bricks
-  __shared__ int origin[K][3];          // first base node of the bricks
-  __shared__ int n_distinct;
-  __shared__ int n_astray;              // some slot has no brick in place
+  __shared__ uint32_t run_tile[K];  // tiles of the first runs
+  __shared__ int16_t run_head[K];   // first slot of those runs
+  __shared__ int origin[K][3];      // first base node of the bricks
+  __shared__ int n_astray;          // some slot has no brick in place
+  constexpr int kCand = 8 + K;      // candidates for a brick placed anew
+  __shared__ uint32_t cand_at[16];
+  __shared__ int votes[K][16];      // of the brick, for a candidate
+  static_assert(kCand <= 16, "candidates");
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -134,7 +156,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   // ---------------------------------------------------------------- G2P
   // Lane pairs to begin with; the chunk's cells may turn out to call for quads.
   int lg = a.lane_group == 4 ? 2 : 1;
-  int slot = fused_slot<NW>(tid, lg);
+  int slot = fused_slot<NW, kRotate>(tid, lg);
   bool in = slot < n_slots;
   // a caller permutation is clamped into [0, P): a bad one gives wrong results, never a fault
   int p = in ? (a.perm ? min(max(a.perm[i0 + slot], 0), (int)(a.P - 1)) : (int)(i0 + slot)) : 0;
@@ -154,12 +176,6 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   bool gather = in && ok;
   cell_of[slot] = gather ? (uint32_t)b0 | ((uint32_t)b1 << 10) | ((uint32_t)b2 << 20) : kNoCell;
   float* const stage = reinterpret_cast<float*>(lds_all) + kStage0;
-  if (lg == 1) {  // (in case the slots are dealt out again)
-    stage[slot] = xp[0];
-    stage[BS + slot] = xp[1];
-    stage[2 * BS + slot] = xp[2];
-    stage[3 * BS + slot] = __int_as_float(p);
-  }
   // every lane's stencil lies in the grid (a flagged or idle lane has base node
   // 0 and the grid at least 3 nodes per axis), so the gathers need no branch;
   // such lanes are zeroed afterwards, only in the wavefronts that hold one
@@ -199,14 +215,19 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     cells = __builtin_amdgcn_readfirstlane(cells);
     const int run = pre + lanes_below(hb) + (head ? 1 : 0) - 1;
     run_of[tid] = (int16_t)run;  // (-1 before the first valid slot)
-    if (head && run < kRuns) {
+    if (head && run < K) {
       run_tile[run] = tile_bits(cell);
       run_head[run] = (int16_t)tid;
     }
   }
   if (lg == 1 && n_slots >= kQuadCell * cells) {  // (uniform)
     lg = 2;
-    slot = fused_slot<NW>(tid, lg);
+    stage[slot] = xp[0];
+    stage[BS + slot] = xp[1];
+    stage[2 * BS + slot] = xp[2];
+    stage[3 * BS + slot] = __int_as_float(p);
+    __syncthreads();
+    slot = fused_slot<NW, kRotate>(tid, lg);
     in = slot < n_slots;
     xp[0] = stage[slot];
     xp[1] = stage[BS + slot];
@@ -221,34 +242,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     __syncthreads();  // the stage is read
   }
   const bool quads = lg == 2;  // (uniform)
-  // Up to K runs of equal tiles take a brick each (in sorted order every tile is one
-  // run).  With more (also when the chunk is in no tile order, and a tile makes several
-  // runs) the first kRuns runs' tiles are deduplicated in order of appearance by
-  // wavefront 0, and the first K distinct ones take the bricks.
-  if (n_runs > K) {  // (uniform)
-    __syncthreads();
-    if (wv == 0) {
-      const int nr = n_runs < kRuns ? n_runs : kRuns;
-      const uint32_t mine = lane < nr ? run_tile[lane] : kNoCell;
-      const int16_t my_head = lane < nr ? run_head[lane] : 0;
-      int first_same = lane;  // first run with this run's tile
-      for (int q = nr - 1; q >= 0; --q)
-        if (q < lane && run_tile[q] == mine) first_same = q;
-      const bool first = lane < nr && first_same == lane;
-      const unsigned long long fb = __ballot(first);
-      // distinct index of a first run = first runs before it; a later run takes its
-      // first run's index (all lanes hold a value, so the shuffle is well defined)
-      const int d_first = lanes_below(fb);
-      const int d = __shfl(d_first, first_same, kWave);
-      if (lane < nr) run_brick[lane] = d;
-      if (first && d < K) {  // (d <= lane; every lane has read its own)
-        run_tile[d] = mine;
-        run_head[d] = my_head;
-      }
-      if (lane == 0) n_distinct = __popcll(fb);
-    }
-  }
-
+  const int put_at = kRotate ? slot : stage_pos(slot, lg);  // of its slot in a staging row
   float c[3][27];  // the new coefficients, kept for the P2G half
   float xn[3];     // the advected position
   // Output rows go through LDS (the bricks are not in use yet) so that every
@@ -261,9 +255,10 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   const int wave = __builtin_amdgcn_readfirstlane(wv);
   auto write_rows = [&](auto rows, int k0, auto dst) {
     if constexpr (kRowMode == kBySlot) {
+      const int get_at = kRotate ? tid : stage_pos(tid, lg);
 #pragma unroll
       for (int k = 0; k < rows; ++k)
-        row_store_nt(row_at(k0 + k)[tid], dst(k), n_slots, tid * (int)sizeof(float));
+        row_store_nt(row_at(k0 + k)[get_at], dst(k), n_slots, tid * (int)sizeof(float));
     } else {
       const int body = rows_body(n_slots);  // (uniform)
       auto each = [&](auto&& put) {
@@ -299,9 +294,9 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       xn[ax] = fminf(x1, g.hi[ax]);
       // rows of this component: x', then the NR coefficients; written once, never re-read
       // here, so streamed past the caches the gathers use
-      row_at(0)[slot] = xn[ax];
+      row_at(0)[put_at] = xn[ax];
 #pragma unroll
-      for (int r = 0; r < NR; ++r) row_at(1 + r)[slot] = c[ax][r];
+      for (int r = 0; r < NR; ++r) row_at(1 + r)[put_at] = c[ax][r];
       __syncthreads();
       // (this workgroup's slots)
       float* const co = a.coeff_out + (size_t)ax * NR * Ps + i0;
@@ -337,8 +332,8 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       for (int e = 0; e < 9; ++e) Fn[e] = 0.0f;
     }
 #pragma unroll
-    for (int e = 0; e < 9; ++e) row_at(e)[slot] = Fn[e];
-    row_at(9)[slot] = m;
+    for (int e = 0; e < 9; ++e) row_at(e)[put_at] = Fn[e];
+    row_at(9)[put_at] = m;
     __syncthreads();
     if (a.F_out)
       write_rows(std::integral_constant<int, 9>{}, 0,
@@ -362,11 +357,9 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     }
   }
   if (!valid) m = 0.0f;
-  const int run_slot = run_of[slot];
-  // brick of this slot's run: the tile's index among the distinct ones
-  const bool dedup = n_runs > K;  // (uniform)
-  const int seg = run_slot < 0 || !dedup ? run_slot : run_slot < kRuns ? run_brick[run_slot] : K;
-  int nb = dedup ? min(n_distinct, K) : n_runs;
+  // the first K runs of equal tiles (in sorted order every tile is one run) take a brick each
+  const int seg = run_of[slot];
+  int nb = min(n_runs, K);
   // this thread's nodes of every brick (it clears and flushes them)
   constexpr int kOwn = kFuseNodes / BS;
   static_assert(kOwn * BS == kFuseNodes, "whole nodes per thread");
@@ -377,7 +370,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
 #pragma unroll
       for (int q = 0; q < kOwn; ++q) brick[k * kFuseV + own_lds + q * (BS / 64) * kFuseSZ] = 0.0;
   };
-  clear_bricks(0, nb * kFuseCh);
+  clear_bricks(0, nb <= kFuseOneRound ? 4 * nb : 2 * nb);
   // in place, a brick's first base node is one below its tile
   const uint32_t cell = cell_of[slot], tl = tile_bits(cell);
   int w0 = (int)(tl & 1023u) - 1, w1 = (int)((tl >> 10) & 1023u) - 1, w2 = (int)(tl >> 20) - 1;
@@ -394,7 +387,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
   }
   if (__ballot(gather && my_brick < 0) != 0ull && lane == 0) n_astray = 1;
   __syncthreads();  // the bricks are clear and placed
-  const bool astray = __builtin_amdgcn_readfirstlane(n_astray) != 0;  // (uniform)
+  const bool astray = n_runs > K || __builtin_amdgcn_readfirstlane(n_astray) != 0;  // (uniform)
   if (astray) {
     // Some slot left its brick, or is past the bricks.  The bricks are then placed anew, one
     // after the other, each on the candidate that holds most of the slots left: the bricks in
@@ -405,22 +398,21 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     // tile moved 3 and 6 cells 257 and 303, all others moved so 266 and 288.  With bricks moved
     // by their tile's first slot 1640; 1358 and 2812, 1528 and 2495.  With bricks on the tiles
     // of the new positions 6443; 273 and 637, 638 and 922).
-    constexpr int kSample = BS / 8, kCand = 8 + K;
-    static_assert(kCand <= 16 && 16 * K <= kRuns, "votes of each brick in run_brick");
+    constexpr int kSample = BS / 8;
     auto pack = [](int o0, int o1, int o2) {  // (a brick that starts below the grid starts on it)
       return (uint32_t)max(o0, 0) | (uint32_t)max(o1, 0) << 10 | (uint32_t)max(o2, 0) << 20;
     };
     if (slot % kSample == 0)
-      run_tile[slot / kSample] =
+      cand_at[slot / kSample] =
           gather ? pack(c0 - 1 - (int)(cell & 3u), c1 - 1 - (int)((cell >> 10) & 3u),
                         c2 - 1 - (int)((cell >> 20) & 3u))
                  : kNoCell;
-    if (heads) run_tile[8 + seg] = pack(w0, w1, w2);
-    if (tid >= nb && tid < K) run_tile[8 + tid] = kNoCell;
-    if (tid < 16 * K) run_brick[tid] = 0;
-    clear_bricks(nb * kFuseCh, K * kFuseCh);
+    if (heads) cand_at[8 + seg] = pack(w0, w1, w2);
+    if (tid >= nb && tid < K) cand_at[8 + tid] = kNoCell;
+    if (tid < 16 * K) votes[tid / 16][tid % 16] = 0;
+    clear_bricks(nb <= kFuseOneRound ? 4 * nb : 2 * nb, kFusePool);
     __syncthreads();
-    const int cand = (int)run_tile[lane & 15];
+    const int cand = (int)cand_at[lane & 15];
     uint32_t fits = 0;  // candidates that hold this slot
 #pragma unroll
     for (int j = 0; j < kCand; ++j) {
@@ -432,15 +424,15 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     my_brick = -1;
     for (nb = 0; nb < K; ++nb) {
       const uint32_t left = my_brick < 0 ? fits : 0u;
-      int votes = 0;  // of this wavefront, for candidate `lane`
+      int mine = 0;  // votes of this wavefront, for candidate `lane`
 #pragma unroll
       for (int j = 0; j < kCand; ++j) {
         const int n = __popcll(__ballot((left >> j) & 1u));
-        votes = lane == j ? n : votes;
+        mine = lane == j ? n : mine;
       }
-      if (votes != 0) atomicAdd(&run_brick[16 * nb + lane], votes);
+      if (mine != 0) atomicAdd(&votes[nb][lane], mine);
       __syncthreads();
-      int most = run_brick[16 * nb + (lane & 15)] << 4 | (15 - (lane & 15));
+      int most = votes[nb][lane & 15] << 4 | (15 - (lane & 15));
 #pragma unroll
       for (int off = 1; off < 16; off <<= 1) most = max(most, __shfl_xor(most, off, kWave));
       most = __builtin_amdgcn_readfirstlane(most);
@@ -460,6 +452,7 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       }
     }
   }
+  const int chn = nb <= kFuseOneRound ? 4 : 2;  // (uniform) channels of a round
   const bool lds = my_brick >= 0;  // (a slot without a brick goes to HBM)
   if (a.regions) {
     // the regions the scatter lands in: the 6^3 nodes of each brick's tile, and those of
@@ -500,11 +493,11 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     const Rows Rz = p2g_rows_scaled(basis_p2g(u2), 1.0f);
     const int lbase = (c0 - w0) + kFuseSY * (c1 - w1) + kFuseSZ * (c2 - w2);
     const int64_t gbase = g.node_off + (int64_t)(c2 * ny + c1) * nx + c0;
-    double* const lb = brick + (lds ? my_brick * kFuseCh * kFuseV + lbase : 0);
+    double* const lb = brick + (lds ? my_brick * chn * kFuseV + lbase : 0);
     // one plane of 9 node values at a time: the folds run on every lane, then a
     // single predicated block per plane does the atomics
     auto emitter = [&](int ch) {
-      double* const lbc = lb + (ch % kFuseCh) * kFuseV;
+      double* const lbc = lb + (ch & (chn - 1)) * kFuseV;
       // (the HBM base is formed only on that rare path, to keep registers free)
       float* const gc = ch == 0 ? a.gm : ch == 1 ? a.gp0 : ch == 2 ? a.gp1 : a.gp2;
       return [=](int jz, float (&v)[9]) {
@@ -542,31 +535,35 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
         }
       };
     };
-    // Flush of a round: one global float atomic per channel per non-zero brick node, by
-    // the node's owner thread, which clears it for the next round.
+    // Flush of two channels of a round: one global float atomic per channel per non-zero brick
+    // node, by the node's owner thread, which clears it for the next round.
     auto flush = [&](int ch0, bool clear) {
       float* const dst[4] = {a.gm, a.gp0, a.gp1, a.gp2};
+      const int own_node = own_x + nx * own_y + nxny * own_z;  // from the brick's corner
       for (int sb = 0; sb < nb; ++sb) {
-        const int gx = origin[sb][0] + own_x;
-        const int gy = origin[sb][1] + own_y;
-        const int gz0 = origin[sb][2] + own_z;
-        if ((unsigned)gx >= (unsigned)nx || (unsigned)gy >= (unsigned)ny) continue;
-        const int64_t node0 = g.node_off + ((int64_t)(gz0 * ny + gy) * nx + gx);
+        // the brick's corner is uniform, so that a node's address is a scalar base and this
+        // thread's offset from the corner
+        const int ox = __builtin_amdgcn_readfirstlane(origin[sb][0]);
+        const int oy = __builtin_amdgcn_readfirstlane(origin[sb][1]);
+        const int oz = __builtin_amdgcn_readfirstlane(origin[sb][2]);
+        const int64_t corner = g.node_off + ((int64_t)oz * ny + oy) * nx + ox;
+        const bool in_xy = (unsigned)(ox + own_x) < (unsigned)nx && (unsigned)(oy + own_y) < (unsigned)ny;
+        double* const src = brick + (sb * chn + (ch0 & (chn - 1))) * kFuseV + own_lds;
 #pragma unroll
         for (int q = 0; q < kOwn; ++q) {
-          double* const src = brick + sb * kFuseCh * kFuseV + own_lds + q * (BS / 64) * kFuseSZ;
-          if ((unsigned)(gz0 + q * (BS / 64)) >= (unsigned)nz) continue;
-          const int64_t node = node0 + q * (BS / 64) * (int64_t)nxny;
-          float v[kFuseCh];
+          double* const at = src + q * (BS / 64) * kFuseSZ;
+          float v[2];
 #pragma unroll
-          for (int k = 0; k < kFuseCh; ++k) v[k] = (float)src[k * kFuseV];
+          for (int k = 0; k < 2; ++k) v[k] = (float)at[k * kFuseV];
           if (clear) {
 #pragma unroll
-            for (int k = 0; k < kFuseCh; ++k) src[k * kFuseV] = 0.0;
+            for (int k = 0; k < 2; ++k) at[k * kFuseV] = 0.0;
           }
+          if (!in_xy || (unsigned)(oz + own_z + q * (BS / 64)) >= (unsigned)nz) continue;
 #pragma unroll
-          for (int k = 0; k < kFuseCh; ++k)
-            if (v[k] != 0.0f) atomicAdd(dst[ch0 + k] + node, v[k]);
+          for (int k = 0; k < 2; ++k)
+            if (v[k] != 0.0f)
+              atomicAdd(dst[ch0 + k] + corner + (unsigned)(own_node + q * (BS / 64) * nxny), v[k]);
         }
       }
     };
@@ -577,17 +574,18 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
       stream_modes_planes<1>(one, Rx, Ry, Rz, emitter(0));
     }
     stream_modes_planes<NR>(c[0], Rx, Ry, Rz, emitter(1));
-    if constexpr (kFuseCh == 2) {
+    if (chn == 2) {
       __syncthreads();
       flush(0, true);
       __syncthreads();
     }
     stream_modes_planes<NR>(c[1], Rx, Ry, Rz, emitter(2));
 #pragma unroll
-    for (int r = NR - kKept; r < NR; ++r) c[2][r] = row_at(1 + r)[slot];  // (this thread's own)
+    for (int r = NR - kKept; r < NR; ++r) c[2][r] = row_at(1 + r)[put_at];  // (this thread's own)
     stream_modes_planes<NR>(c[2], Rx, Ry, Rz, emitter(3));
     __syncthreads();
-    flush(4 - kFuseCh, false);
+    if (chn == 4) flush(0, false);
+    flush(2, false);
   }
 }
 

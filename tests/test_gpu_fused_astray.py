@@ -106,3 +106,35 @@ def test_a_jet_leaves_the_others_in_their_bricks():
     ms(0.0)
     note(f"fused jet: rest {ms(0.0):.4f} ms, 3 cells {ms(3.0):.4f} ms")
     assert ms(3.0) <= 2.5 * ms(0.0)
+
+
+@pytest.mark.parametrize("n_modes", [1, 4, 8, 27])
+@pytest.mark.parametrize("tiles", [(256,), (255, 1), (100, 156), (3, 200, 53), (64, 64, 64, 64),
+                                   (1, 1, 1, 253), (40,) * 6 + (16,), (256, 100, 156, 37)])
+def test_chunks_of_one_tile_and_more(tiles, n_modes):
+    """Chunks whose slots lie in one tile (one round of the scatter, all channels), in two or
+    three (two rounds), and in more than there are bricks; at the grid's corner and inside it."""
+    pp = require_gpu()
+    note(f"fused rounds: {tiles} n_modes={n_modes}")
+    n = 40
+    rng = np.random.default_rng(sum(tiles) + n_modes)
+    corner = [(4 * (k % 3), 4 * (k // 3), 4 * (k % 2)) for k in range(len(tiles))]
+    x = np.concatenate([(1.0 + np.array(corner[k])[:, None] + 3.98 * rng.random((3, m)))
+                        for k, m in enumerate(tiles)], 1)
+    x = (np.maximum(x, 2.001) / n).astype(np.float32)
+    P, N = x.shape[1], n + 4
+    g = pp.make_grid((N,) * 3, 1.0 / n)
+    og = oracle_grid(g)
+    gv = (0.05 * rng.uniform(-1, 1, (3, N, N, N)) / n).astype(np.float32)
+    f = lambda *s: torch.full(s, 7.0, device="cuda")  # noqa: E731
+    xo, co, gm, gp = f(3, P), f(3, n_modes, P), f(N ** 3), f(3 * N ** 3)
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    pp.ops.polypic_g2p2g(g, n_modes, 1.0, dev(gv).reshape(-1), dev(x), xo, co, gm, gp,
+                         status_dev=st)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    c_ref, x_ref, _ = O.g2p(og, gv.astype(np.float64), x, n_modes, 1.0)
+    assert rel(host(co), c_ref) <= TOL_NORMWISE
+    M_ref, Q_ref = O.p2g(og, host(xo), host(co), n_modes)
+    assert rel(host(gm).reshape(M_ref.shape), M_ref) <= TOL_NORMWISE
+    assert rel(host(gp).reshape(Q_ref.shape), Q_ref) <= TOL_NORMWISE
