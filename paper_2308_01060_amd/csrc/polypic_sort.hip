@@ -528,6 +528,7 @@ __global__ __launch_bounds__(kSmallBS) void small_sort_kernel(
   __shared__ uint16_t whist[kSmallWaves][kRadix];  // per wave: running digit counts
   __shared__ uint32_t digit_base[kRadix];
   __shared__ uint32_t wsum[kRadix / kWave];
+  __shared__ int wave_moves[kSmallWaves];  // does the wave hold a key that changed?
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wv = tid / kWave;
@@ -550,7 +551,7 @@ __global__ __launch_bounds__(kSmallBS) void small_sort_kernel(
       before[j] = keys_prev && i > 0 ? keys_prev[i - 1] : 0u;
     }
     int s = sc.first(min(base, P - 1));
-    bool in_range = true, in_order = true;
+    bool in_range = true, in_order = true, changed = keys_prev == nullptr;
 #pragma unroll
     for (int j = 0; j < kSortIPT; ++j) {
       if (j >= rounds) break;
@@ -560,15 +561,22 @@ __global__ __launch_bounds__(kSmallBS) void small_sort_kernel(
       val[j] = (uint32_t)i;
       in_range &= ok;
       in_order &= before[j] <= prev[j];
+      changed |= key[j] != prev[j];
     }
     if (!in_range) raise_flag(status, kFlagRange);
     if (!in_order) raise_flag(status, kFlagOrder);
+    const unsigned long long moves = __ballot(changed || !in_order);
+    if (lane == 0) wave_moves[wv] = moves != 0ull;
   }
   for (int q = 0; q < passes; ++q) {
     const int shift = 8 * q;
     for (int k = tid; k < kSmallWaves * kRadix / 2; k += kSmallBS)
       reinterpret_cast<uint32_t*>(&whist[0][0])[k] = 0u;
     __syncthreads();
+    // A re-sort of keys that did not change (a set at rest) has nothing to move.  (Measured,
+    // 8,192 unchanged slots with 4 digits: 28 us in the launches of the larger re-sort, 31 in 4
+    // passes here, 10 with none; 3 % changed 46 and 31.)
+    if (q == 0 && __ballot(wave_moves[lane & (kSmallWaves - 1)] != 0) == 0ull) break;  // (uniform)
 #pragma unroll
     for (int j = 0; j < kSortIPT; ++j) {
       if (j >= rounds) break;
