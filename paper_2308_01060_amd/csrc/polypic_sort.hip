@@ -913,9 +913,12 @@ __device__ __forceinline__ int64_t wave_lower_pair(KeyAt kat, IdxAt iat, int64_t
 // each), then every lane searches the few hundred slots between them, which
 // neighbouring lanes read together.  (One pair per wavefront, each searched over
 // all slots, was bound by those round trips: at 16.8 M slots and 3 % changed it
-// took 0.84 ms, now 0.08; at
-// 4.2 M and 3 %, 59 and 11 us, over the unchanged slots' time.)  Lists too short to fill the launch's wavefronts at 64 pairs each keep
-// one pair per wavefront: they are bound by one pair's chain of round trips.
+// took 0.84 ms, now 0.08; at 4.2 M and 3 %, 59 and 11 us, over the unchanged
+// slots' time.)  A list of no more pairs than the launch has wavefronts (4,096)
+// keeps one pair per wavefront: one chain of round trips, where a lane's is
+// longer (measured, whole re-sort of 4.2 M slots, a pair per wavefront and per
+// lane: 500 changed 51 and 55 us, 2,000 55 and 57, 4,000 61 and 61, 5,000 63 and
+// 61, 8,000 67 and 63).
 __device__ __forceinline__ void place_changed(
     int blk, int n_blk, int64_t P, const uint32_t* __restrict__ keys_prev,
     const unsigned long long* __restrict__ mask, const uint32_t* __restrict__ gpre,
@@ -932,7 +935,7 @@ __device__ __forceinline__ void place_changed(
     keys_out[pos] = key;
     perm_out[pos] = idx;
   };
-  if ((int64_t)M <= 2 * waves) {  // (uniform)
+  if ((int64_t)M <= waves) {  // (uniform)
     for (int64_t j = wave; j < (int64_t)M; j += waves) {
       const uint32_t key = cks[j];
       const int32_t idx = cvs[j];
