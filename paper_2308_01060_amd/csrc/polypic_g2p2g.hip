@@ -597,13 +597,14 @@ hipError_t launch_nr(const G2P2GArgs& a, const Scenes& sc, unsigned blocks, hipS
   // lines: P = 1234567 173 and 131 us, 2500007 305 and 240, 4000037 484 and 409; P = 2500008
   // 260 and 265, 4000040 406 and 450; at 4 modes, P = 2500007, 153 and 168).  The rows' ends
   // go through the caches while those still hold a line when the neighbouring workgroup's
-  // part of it comes: up to about 4.2 M particles (through the caches and streamed:
-  // 3400007 358 and 380 us, 4000037 409 and 422, 4194303 478 and 458, 5500001 629 and 581).
+  // part of it comes: up to about 4 M particles (through the caches and streamed: 2500007 257
+  // and 274 us, 3400007 339 and 380, 3900003 414 and 419, 4000037 435 and 431, 4100009 470 and
+  // 447, 4194303 460 and 463, 5500001 629 and 581).
   // A batch's workgroups neighbour each other on one XCD, whose L2 joins the parts of a
   // line: 718 us a slot per thread, 745 in lines.
   if constexpr (NR == 27 && std::is_same_v<Scenes, OneScene>) {
     if (rows_want_lines(NR, 32, a.P, {a.coeff_out, a.x_out})) {
-      if (a.P < (int64_t)1 << 22)
+      if (a.P < 4000000)
         g2p2g_kernel<NR, BS, Scenes, kLinesCached><<<blocks, BS, 0, stream>>>(a, sc);
       else
         g2p2g_kernel<NR, BS, Scenes, kLinesStream><<<blocks, BS, 0, stream>>>(a, sc);
