@@ -43,6 +43,13 @@ constexpr int kMacV = (kMacN - 1) * (1 + kMacSY + kMacSZ) + 1;  // doubles per c
 constexpr int kMacCh = 2;   // channels of a round
 constexpr int kMacK = 3;    // bricks per workgroup
 constexpr int kMacBS = 256;
+// A launch of few workgroups takes a component in each (blockIdx.y) instead of all three one
+// after the other: it is bound by a workgroup's own latency, which the three rounds' barriers
+// and flushes lengthen.  Up to the workgroups whose three fit on the card at once, 512 of its
+// 1,536 (256 CUs, 6 by LDS; measured, all six channels in one round, three rounds, and a
+// component each, 27 modes: 1,728 particles 17.9, 19.8 and 9.3 us, 32,768 48, 35 and 26,
+// 125,000 36, 26.7 and 25.8, 262,144 88, 54.5 and 56.6).
+constexpr unsigned kMacSplit = 512;
 
 // u = (x - o) inv_dx with two float32 roundings; the node stencil (b, t) and the
 // stencil of the lattice shifted by +dx/2 (bs, ts); false if either leaves [0, n - 3].
@@ -118,8 +125,10 @@ __global__ __launch_bounds__(kMacBS, 4) void mac_p2g_kernel(MacP2GArgs a) {
   const int nb = plan.n_bricks < kMacK ? plan.n_bricks : kMacK;
   // Every lane runs the component loop (an idle one with zero mass and coefficients),
   // since the pair folds read the partner lane through DPP.
+  // all components, or the workgroup's own
+  const int ax0 = gridDim.y == 3 ? (int)blockIdx.y : 0, ax1 = gridDim.y == 3 ? ax0 + 1 : 3;
 #pragma unroll 1
-  for (int ax = 0; ax < 3; ++ax) {
+  for (int ax = ax0; ax < ax1; ++ax) {
     float c[27];
 #pragma unroll
     for (int r = 0; r < 27; ++r) c[r] = 0.0f;
@@ -192,7 +201,7 @@ __global__ __launch_bounds__(kMacBS, 4) void mac_p2g_kernel(MacP2GArgs a) {
         if (vp != 0.0) atomicAdd(a.fp + f, (float)vp);
       }
     }
-    if (ax < 2) __syncthreads();
+    if (ax + 1 < ax1) __syncthreads();
   }
 }
 
@@ -325,7 +334,7 @@ __global__ __launch_bounds__(256) void mac_grid_update_kernel(MacUpdateArgs a) {
 template <int NR>
 hipError_t mac_p2g_nr(const MacP2GArgs& a, hipStream_t s) {
   const unsigned blocks = (unsigned)((a.P + kMacBS - 1) / kMacBS);
-  mac_p2g_kernel<NR><<<blocks, kMacBS, 0, s>>>(a);
+  mac_p2g_kernel<NR><<<dim3(blocks, blocks <= kMacSplit ? 3 : 1), kMacBS, 0, s>>>(a);
   return hipGetLastError();
 }
 
