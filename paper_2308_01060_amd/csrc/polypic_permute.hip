@@ -15,7 +15,8 @@ namespace {
 
 constexpr int kPermBlock = 256;
 constexpr int kPermUnroll = 8;      // whole: rows in flight per thread
-constexpr int kPermRows = 6;        // groups: rows of a workgroup, in flight together
+// groups: rows of a workgroup, in flight together
+constexpr int kGatherRows = 4, kScatterRows = 6;
 constexpr int64_t kPermWhole = 64;  // most rows that a thread goes through by itself
 
 // One thread per slot, the slots in XCD-contiguous order: the indexed side of neighbouring
@@ -32,9 +33,10 @@ constexpr int64_t kPermWhole = 64;  // most rows that a thread goes through by i
 // that go through all rows in launch order, in groups of 4 rows, and as here.  4.19 M slots: 1
 // row gathered 10, 14 and 10, scattered 11, 17 and 11; 4 rows scattered 24, 27 and 23, in
 // random order 202, 400 and 202; 9 rows gathered 47, 56 and 47; 81 rows gathered 572, 518 and
-// 482, scattered 630, 518 and 513, in random order 13160, 6909 and 6979.  1.77 M slots in
+// 510, scattered 630, 518 and 513, in random order 13160, 6909 and 6979.  1.77 M slots in
 // random order, scattered: 12 rows 330, 494 and 326; 40 rows 1225, 1408 and 1186, where groups
-// of 6 take 1463; 81 rows 3918, 2679 and 2693.)
+// of 6 take 1463; 81 rows 3918, 2679 and 2693.  Groups of 4 and of 6 rows, 81 rows of 1.77 M
+// slots whose order differs by a few hundred slots: gathered 259 and 283, scattered 332 and 314.)
 struct PermSlot {
   int64_t i, p;  // slot, and the particle it indexes
 };
@@ -55,13 +57,13 @@ __global__ __launch_bounds__(kPermBlock) void gather_rows_kernel(const uint32_t*
   PermSlot at;
   if (!perm_slot(idx, P, at)) return;
   if constexpr (kGroups) {
-    for (int64_t r = (int64_t)blockIdx.y * kPermRows; r < rows; r += (int64_t)gridDim.y * kPermRows) {
-      uint32_t v[kPermRows];
+    for (int64_t r = (int64_t)blockIdx.y * kGatherRows; r < rows; r += (int64_t)gridDim.y * kGatherRows) {
+      uint32_t v[kGatherRows];
 #pragma unroll
-      for (int k = 0; k < kPermRows; ++k)
+      for (int k = 0; k < kGatherRows; ++k)
         if (r + k < rows) v[k] = src[(r + k) * P + at.p];
 #pragma unroll
-      for (int k = 0; k < kPermRows; ++k)
+      for (int k = 0; k < kGatherRows; ++k)
         if (r + k < rows) __builtin_nontemporal_store(v[k], dst + (r + k) * P + at.i);
     }
   } else {
@@ -87,13 +89,13 @@ __global__ __launch_bounds__(kPermBlock) void scatter_rows_kernel(const uint32_t
   PermSlot at;
   if (!perm_slot(idx, P, at)) return;
   if constexpr (kGroups) {
-    for (int64_t r = (int64_t)blockIdx.y * kPermRows; r < rows; r += (int64_t)gridDim.y * kPermRows) {
-      uint32_t v[kPermRows];
+    for (int64_t r = (int64_t)blockIdx.y * kScatterRows; r < rows; r += (int64_t)gridDim.y * kScatterRows) {
+      uint32_t v[kScatterRows];
 #pragma unroll
-      for (int k = 0; k < kPermRows; ++k)
+      for (int k = 0; k < kScatterRows; ++k)
         if (r + k < rows) v[k] = __builtin_nontemporal_load(src + (r + k) * P + at.i);
 #pragma unroll
-      for (int k = 0; k < kPermRows; ++k)
+      for (int k = 0; k < kScatterRows; ++k)
         if (r + k < rows) dst[(r + k) * P + at.p] = v[k];
     }
   } else {
@@ -110,8 +112,8 @@ __global__ __launch_bounds__(kPermBlock) void scatter_rows_kernel(const uint32_t
   }
 }
 
-dim3 perm_grid(int64_t rows, int64_t P) {
-  const int64_t groups = rows <= kPermWhole ? 1 : (rows + kPermRows - 1) / kPermRows;
+dim3 perm_grid(int64_t rows, int64_t P, int per) {
+  const int64_t groups = rows <= kPermWhole ? 1 : (rows + per - 1) / per;
   return dim3((unsigned)((P + kPermBlock - 1) / kPermBlock),
               (unsigned)(groups < 65535 ? groups : 65535));
 }
@@ -130,7 +132,7 @@ hipError_t launch_gather_rows(const void* src, void* dst, const int32_t* idx, in
                               int64_t P, hipStream_t stream) {
   if (P == 0 || rows == 0) return hipSuccess;
   (rows <= kPermWhole ? gather_rows_kernel<false> : gather_rows_kernel<true>)
-      <<<perm_grid(rows, P), kPermBlock, 0, stream>>>(
+      <<<perm_grid(rows, P, kGatherRows), kPermBlock, 0, stream>>>(
           static_cast<const uint32_t*>(src), static_cast<uint32_t*>(dst), idx, rows, P);
   return hipGetLastError();
 }
@@ -139,7 +141,7 @@ hipError_t launch_scatter_rows(const void* src, void* dst, const int32_t* idx, i
                                int64_t P, hipStream_t stream) {
   if (P == 0 || rows == 0) return hipSuccess;
   (rows <= kPermWhole ? scatter_rows_kernel<false> : scatter_rows_kernel<true>)
-      <<<perm_grid(rows, P), kPermBlock, 0, stream>>>(
+      <<<perm_grid(rows, P, kScatterRows), kPermBlock, 0, stream>>>(
           static_cast<const uint32_t*>(src), static_cast<uint32_t*>(dst), idx, rows, P);
   return hipGetLastError();
 }
