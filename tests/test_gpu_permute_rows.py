@@ -1,5 +1,5 @@
 """Row permutations at the row counts where the kernels change course (whole runs of eight rows and
-the rows after them, by the thread that has the slot; groups of rows from 65 on), against
+the rows after them, by the thread that has the slot; groups of rows above that), against
 indexing, bit for bit; and the cost of a few rows scattered in no order."""
 import pytest
 import torch
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("P", [1, 255, 257, 2304, 5001])
-@pytest.mark.parametrize("rows", [1, 7, 8, 9, 16, 23, 63, 64, 65, 66, 71, 72, 73])
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 15, 16, 17, 18, 19, 23, 63, 64, 65, 66, 71, 72, 73])
 def test_rows_equal_indexing(rows, P):
     pp = require_gpu()
     note(f"permute rows={rows} P={P}")
