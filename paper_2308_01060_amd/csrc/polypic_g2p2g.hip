@@ -64,17 +64,17 @@ __device__ __forceinline__ int stage_pos(int s, int lg) {
 // then stays in its own tile's brick.  With bricks of the tile alone (6^3 nodes), given to
 // the tiles of the new positions, such particles take a chunk past its bricks and go to
 // HBM, 27 atomics per channel each, and the call slows with the speed of the flow
-// (measured, 4.19 M particles, 4 modes, 0.1, 1.3 and 2.6 % of a cell per step and axis: 232,
-// 478 and 756 us; with these bricks 215, 249 and 275).  The z stride spreads a half wavefront's
-// cells over the banks, as in the tile-only bricks.
+// (measured, 4.19 M particles, 4 modes, 0.1, 1.3 and 2.6 % of a cell per step and axis: 237,
+// 507 and 860 us; with these bricks 208, 234 and 258; at rest 188 and 185).  The z stride
+// spreads a half wavefront's cells over the banks, as in the tile-only bricks.
 constexpr int kFuseN = kBrickN + 2;  // nodes per brick edge
 constexpr int kFuseSY = 8;
 constexpr int kFuseSZ = 68;
 constexpr int kFuseV = (kFuseN - 1) * (1 + kFuseSY + kFuseSZ) + 1;  // doubles per channel
 constexpr int kFuseNodes = kFuseN * kFuseN * kFuseN;
 // A round of the scatter fills two channels: two rounds let three bricks fit where all four
-// channels at once would leave two, and a chunk of a block's edge or of a
-// small scene touches three or four tiles (of a 16^3-cell block's slots, 4.5 % lie in the
+// channels at once would leave two, and a chunk of a block's edge or of a small scene touches
+// three or four tiles (of a 16^3-cell block's slots, 4.5 % lie in the
 // third tile of their chunk or later, 0.9 % in the fourth or later).
 constexpr int kFuseK = 3;  // bricks per workgroup
 // All four channels of one brick fit in two rounds' space of three: a chunk of one brick (a
@@ -87,7 +87,9 @@ constexpr int kFuseBrickF = (2 * kFusePool * kFuseV + 63) / 64 * 64;  // in floa
 // they were staged in, instead of holding them in registers across the scatter of the
 // other channels: at 27 modes the 128 registers of 4 waves per SIMD otherwise spill, and
 // the spills' scratch traffic costs more than these reads (measured, 27 modes: 414 us at
-// 11 spilled registers, 385 at none; 776 and 718 for a batch of 6 M particles).
+// 11 spilled registers, 385 at none; 776 and 718 for a batch of 6 M particles).  (The instance
+// of one scene that writes slot by slot spills one register for the permuted stage: 377 us
+// rotated and without it, 374 so.)
 template <int NR>
 constexpr int kFuseKept = NR > 8 ? 12 : 0;
 constexpr uint32_t kNoCell = 0xFFFFFFFFu;
@@ -97,19 +99,20 @@ constexpr int kQuadCell = 10;  // particles per cell of a chunk from which quads
 
 // LDS (about 40 KB per 256-thread workgroup at 27 modes) allows 4 waves per SIMD; the
 // launch bound holds the registers to the 128 that allow them too (measured, 4.19 M
-// particles: 0.40 ms at 3 waves per SIMD, 0.38 ms at 4).  With at most 8 modes 28 KB and
-// fewer registers allow 5.
+// particles: 0.40 ms at 3 waves per SIMD, 0.38 ms at 4).  With at most 8 modes 28 KB and, for
+// one scene, fewer registers allow 5 (a whole step at 4 modes 291 us, 309 where LDS holds it
+// to 4); the batch's instances at 4 and 8 modes need the registers of 4.
 // Lane groups: a group whose particles share brick and base node adds its node values
 // across lanes first, and one lane does the atomics.  A pair adds in 32 bits, a quad's two
 // pairs in 64, as the bricks (their sums then hold the bits that pairs leave; measured, 32 and
 // 64 bits for the second sum, 4.19 M particles at 16 per cell: 4 modes 240 and 233 us, 27 modes
-// 387 and 398).  Pairs do best while the 32 pairs of
-// a wavefront fall in different cells (one DPP fold per node value instead of two); in
-// chunks whose cells hold more particles two pairs of a wavefront share a cell and its LDS
-// addresses, and quads do better.  By default (lane_group 2) the kernel counts the
-// cells of each chunk and takes quads from kQuadCell particles per cell on (measured, pairs
-// and quads, 27 modes: 194 and 207 us at 8 per cell, 330 and 323 at 12, 457 and 419 at 16;
-// 4 modes: 238 and 203 at 12, 330 and 251 at 16).
+// 387 and 398).  Pairs do best while the 32 pairs of a wavefront fall in different cells (one
+// DPP fold per node value instead of two); in chunks whose cells hold more particles two pairs
+// of a wavefront share a cell and its LDS addresses, and quads do better.  By default
+// (lane_group 2) the kernel counts the cells of each chunk and takes quads from kQuadCell
+// particles per cell on (measured, pairs and quads, 27 modes: 195 and 207 us at 8 per cell, 301
+// and 299 at 12, 405 and 382 at 16; 4 modes: 120 and 134 at 8, 219 and 186 at 12, 308 and 230
+// at 16).
 // kRowMode: how the output rows are written.
 constexpr int kBySlot = 0;       // every thread its slot of each row
 constexpr int kLinesCached = 1;  // in whole lines, the rows' ends through the caches
@@ -393,11 +396,11 @@ __global__ __launch_bounds__(BS, 4) void g2p2g_kernel(G2P2GArgs a, Scenes sc) {
     // after the other, each on the candidate that holds most of the slots left: the bricks in
     // place, and the tiles of eight slots of the chunk moved as those slots moved.  A flow of
     // several cells per step moves a tile's particles alike; a splash or a jet moves a few of
-    // them, and the others are to stay in their brick (measured, 4.19 M particles, 4 modes, 192
-    // us at rest: a smooth flow of 1.3 cells per step and axis 454 us; the first cell of every
-    // tile moved 3 and 6 cells 257 and 303, all others moved so 266 and 288.  With bricks moved
-    // by their tile's first slot 1640; 1358 and 2812, 1528 and 2495.  With bricks on the tiles
-    // of the new positions 6443; 273 and 637, 638 and 922).
+    // them, and the others are to stay in their brick (measured, 4.19 M particles, 4 modes, 185
+    // us at rest: a smooth flow of 1.3 and 3.8 cells per step and axis 451 and 789 us; the first
+    // cell of every tile moved 3 and 6 cells 249 and 301, all others moved so 260 and 286.  With
+    // bricks moved by their tile's first slot 1686 and 4631; 1389 and 2884, 1578 and 2572.  With
+    // bricks on the tiles of the new positions 6575 and 7536; 277 and 650, 641 and 928).
     constexpr int kSample = BS / 8;
     auto pack = [](int o0, int o1, int o2) {  // (a brick that starts below the grid starts on it)
       return (uint32_t)max(o0, 0) | (uint32_t)max(o1, 0) << 10 | (uint32_t)max(o2, 0) << 20;

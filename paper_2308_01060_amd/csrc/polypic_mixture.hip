@@ -88,8 +88,9 @@ __global__ __launch_bounds__(kMixBS, 4) void mixture_p2g_kernel(MixtureP2GArgs a
                                          (uint32_t)((b[2] * 1024 + b[1]) * 1024 + b[0]));
   // Chunks of dense cells fold quads, dealt out four slots to a quad: as pairs, two of a
   // wavefront would share a cell and its LDS addresses (the positions are read again, from
-  // the caches; measured, pairs and quads, 2.35 M particles at 16 per cell: 27 modes 280 and
-  // 259 us, 4 modes 192 and 158; 1.5 M at 12: 177 and 166).
+  // the caches; measured, pairs and quads, 27 modes: 2.35 M particles at 16 per cell 297 and 283
+  // us, 1.82 M at 12 238 and 227, 1.3 M at 8 185 and 180; 4 modes 207 and 169, 165 and 148, 132
+  // and 136).
   const int n_slots = (int)min((int64_t)BS, a.P - (int64_t)blockIdx.x * BS);
   const bool quads = n_slots >= kMixQuadCell * plan_cells(plan);  // (uniform)
   if (quads) {
