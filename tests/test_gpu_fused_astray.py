@@ -138,3 +138,37 @@ def test_chunks_of_one_tile_and_more(tiles, n_modes):
     M_ref, Q_ref = O.p2g(og, host(xo), host(co), n_modes)
     assert rel(host(gm).reshape(M_ref.shape), M_ref) <= TOL_NORMWISE
     assert rel(host(gp).reshape(Q_ref.shape), Q_ref) <= TOL_NORMWISE
+
+
+@pytest.mark.parametrize("n_modes", [4, 27])
+@pytest.mark.parametrize("chunks", [256, 257])
+@pytest.mark.parametrize("past", [64, 65])
+def test_slots_without_a_brick_in_small_launches(past, chunks, n_modes):
+    """Chunks of four tiles whose last one, past the bricks, holds a quarter of the slots or one
+    more: the bricks are placed anew for either in a launch of 257 workgroups, and only for more
+    than a quarter in one of 256."""
+    pp = require_gpu()
+    note(f"fused small launch: {past} past the bricks, {chunks} chunks, n_modes={n_modes}")
+    n = 40
+    rng = np.random.default_rng(past + chunks + n_modes)
+    t = np.repeat(np.arange(4 * chunks) % 512, np.tile([64, 64, 128 - past, past], chunks))
+    tile = 4.0 * np.stack([t % 8, t // 8 % 8, t // 64])
+    x = np.maximum(1.0 + tile + 3.98 * rng.random((3, len(t))), 2.001)
+    x = (x / n).astype(np.float32)
+    P, N = x.shape[1], n + 4
+    g = pp.make_grid((N,) * 3, 1.0 / n)
+    og = oracle_grid(g)
+    gv = (0.05 * rng.uniform(-1, 1, (3, N, N, N)) / n).astype(np.float32)
+    f = lambda *s: torch.full(s, 7.0, device="cuda")  # noqa: E731
+    xo, co, gm, gp = f(3, P), f(3, n_modes, P), f(N ** 3), f(3 * N ** 3)
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    pp.ops.polypic_g2p2g(g, n_modes, 1.0, dev(gv).reshape(-1), dev(x), xo, co, gm, gp,
+                         status_dev=st)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    c_ref, x_ref, _ = O.g2p(og, gv.astype(np.float64), x, n_modes, 1.0)
+    assert rel(host(co), c_ref) <= TOL_NORMWISE
+    assert ulp_ok(host(xo), x_ref, 2, 1.5)
+    M_ref, Q_ref = O.p2g(og, host(xo), host(co), n_modes)
+    assert rel(host(gm).reshape(M_ref.shape), M_ref) <= TOL_NORMWISE
+    assert rel(host(gp).reshape(Q_ref.shape), Q_ref) <= TOL_NORMWISE
